@@ -117,6 +117,75 @@ static void ntt_domain_keys(const mm_ctx &c, const NttTables &T, const uint32_t 
     });
 }
 
+// x mod Q as the residue of least magnitude.
+static int32_t centred(uint32_t x, uint32_t Q) { return x > (Q - 1) / 2 ? (int32_t)(x - Q) : (int32_t)x; }
+
+// Byte j of the four balanced bytes of x (|x| < 2^30): x = sum_j byte_j 2^(8 j).
+static uint32_t balanced_byte(int32_t x, int j)
+{
+    return ((((uint32_t)x + 0x80808080u) ^ 0x80808080u) >> (8 * j)) & 255u;
+}
+
+// The matrix-core step exists for N = 1024 at the 31-bit modulus with digits whose
+// balanced value fits a signed byte (fields up to B, minus B/2: B <= 2^7), and where
+// the 64-bit sums of a key's 2l products stay below 2^63 with the folded sums of the
+// key before.  Products: |X| <= Q/2 + 2^13, |K| <= Q/2; fold: 2^31 |2^32 mod Q| + 2^32.
+static bool mx_applies(const mm_ctx &c)
+{
+    const mm_params &p = c.p;
+    if (c.wide || p.N != 1024 || p.log2_B > 7 || p.l > dev::MX_MAX_L) return false;
+    const unsigned __int128 half = p.Q / 2, two32 = (unsigned)std::abs(centred(to_mont(1, p.Q), p.Q));
+    const unsigned __int128 sums = (unsigned __int128)(2 * p.l) * (half + 8192 + 1) * half;
+    const unsigned __int128 fold = c.keys == 2 ? ((unsigned __int128)two32 << 31) + ((unsigned __int128)1 << 32) : 0;
+    return sums + fold < ((unsigned __int128)1 << 63);
+}
+
+// The constant block of kernels_mx.hip.  An operand is 64 lanes x 16 bytes: byte b of
+// lane (c, h) belongs to column (or row) c of the constant and to contraction index
+// 16 h + b of the 32 of one instruction; twiddles are words.
+static std::vector<uint32_t> mx_tables(const mm_ctx &c)
+{
+    const uint32_t Q = c.p.Q, N = 1024, psi = c.ntt.psi;
+    std::vector<uint32_t> pw(2 * N), out(dev::MX_CONST_WORDS, 0);
+    pw[0] = 1;
+    for (uint32_t k = 1; k < 2 * N; k++) pw[k] = mulmod(pw[k - 1], psi, Q);
+    auto at = [&](int64_t e) { return pw[(size_t)(((e % (2 * (int64_t)N)) + 2 * N) % (2 * N))]; };
+    auto put = [&](int op, uint32_t lane, uint32_t b, uint32_t byte) {
+        out[((size_t)op * 64 + lane) * 4 + b / 4] |= byte << (8 * (b % 4));
+    };
+    auto word = [&](uint32_t op, uint32_t lane, uint32_t s, uint32_t w, uint32_t skip = 0) {  // w and 2^16 w, Montgomery form
+        const uint32_t f = to_mont(w, Q);
+        out[((size_t)op * 64 + lane + skip) * 4 + s] = (uint32_t)centred(f, Q);
+        out[((size_t)(op + 1) * 64 + lane + skip) * 4 + s] = (uint32_t)centred(mulmod(f, 65536 % Q, Q), Q);
+    };
+    for (uint32_t lane = 0; lane < 64; lane++) {
+        const uint32_t col = lane % 32, h = lane / 32;
+        for (uint32_t q = 0; q < 4; q++)
+            for (uint32_t s = 0; s < 4; s++) {
+                const int64_t row = 8 * q + 4 * h + s;
+                // first stage: digits x[32 row + i2], byte 4 q + s of half h
+                for (int j = 0; j < 4; j++)
+                    put(j, lane, 4 * q + s, balanced_byte(centred(at(32 * row * (2 * col + 1)), Q), j));
+                // second stage, rows (4 q + s) of half h, byte m of the residue
+                for (int m = 0; m < 4; m++) {
+                    const int32_t w = centred(mulmod(at(64 * row * col), (uint32_t)((1ull << (8 * m)) % Q), Q), Q);
+                    for (int j = 0; j < 4; j++) put(4 + 4 * (int)q + j, lane, 4 * s + m, balanced_byte(w, j));
+                }
+                // twiddles of the value at (row, column): forward (i2, k1), inverse (k1, i2);
+                // factors of the last inverse stage's rows i1
+                word(20 + 2 * q, lane, s, at(row * (2 * col + 1)));
+                word(28 + 2 * q, lane, s, at(-(int64_t)col * (2 * row + 1)), 16);
+                if (col == 0) {
+                    const size_t o = ((size_t)28 * 64 + 4 * q + 2 * h) * 4 + s;
+                    const uint32_t f = to_mont(at(-32 * row), Q);
+                    out[o] = (uint32_t)centred(f, Q);
+                    out[o + 4] = (uint32_t)centred(mulmod(f, 65536 % Q, Q), Q);
+                }
+            }
+    }
+    return out;
+}
+
 void device_init(mm_ctx &c, int id)
 {
     if (c.dev && c.dev->id == id) return;
@@ -195,6 +264,17 @@ void device_init(mm_ctx &c, int id)
     }
     upload(&d->bsk, kb.data(), kb.size());
     upload(&d->bsk_corr, corr.data(), corr.size());
+    if (mx_applies(c)) {
+        const std::vector<uint32_t> cst = mx_tables(c);
+        upload(&d->mx_cst, cst.data(), cst.size());
+        if (hipMalloc((void **)&d->mx_bsk, kb.size() * 4) != hipSuccess) {
+            d->mx_bsk = nullptr;
+            throw Error(MM_ENOMEM, "device key allocation failed");
+        }
+        dev::launch_mx_keys(d->bsk, d->mx_bsk, kb.size() / N, Q, d->qn, to_mont(to_mont(1, Q), Q), nullptr);
+        HIPC(hipGetLastError());
+        HIPC(hipDeviceSynchronize());
+    }
     {
         // the key-switching key in column tiles, [i][tile][l_ks B_ks][64], a few
         // coordinates at a time through a host buffer
@@ -289,11 +369,14 @@ static void finish_out(uint32_t *host, const uint32_t *dev, size_t words, bool d
 // ciphertext k with comp = 0; the result holds gw tasks per group, the wpp
 // waves of a slot carrying the same task.  With cap < slots a group takes at
 // most cap components (a wider ciphertext still gets a group of its own), so
-// that a small batch spreads over more compute units, one wave per SIMD.
-std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uint32_t gw, uint32_t wpp, uint32_t cap)
+// that a small batch spreads over more compute units, one wave per SIMD; the cap
+// holds after the first `full` components, which fill whole groups.
+std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uint32_t gw, uint32_t wpp, uint32_t cap,
+                                      uint64_t full)
 {
-    const uint32_t slots = gw / wpp;
-    cap = std::max<uint32_t>(1, std::min(cap ? cap : slots, slots));
+    const uint32_t slots = gw / wpp, thin = std::max<uint32_t>(1, std::min(cap ? cap : slots, slots));
+    cap = full ? slots : thin;
+    uint64_t placed = 0;
     for (auto &t : cts)
         MM_REQUIRE(t.r >= 1 && t.r <= slots,
                    "a ciphertext's r components times their waves per component must fit one workgroup");
@@ -304,7 +387,13 @@ std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uin
     std::vector<uint32_t> used;  // slots used per group
     size_t first_open = 0;
     for (size_t o : order) {
+        if (full && placed >= full) {
+            full = 0;
+            cap = thin;
+            first_open = used.size();
+        }
         const uint32_t r = cts[o].r, limit = std::max(cap, r);
+        placed += r;
         size_t g = first_open;
         while (g < used.size() && used[g] + r > limit) g++;
         if (g == used.size()) {
@@ -353,7 +442,11 @@ static std::vector<dev::WaveTask> pack_groups(const mm_ctx &c, const Device &d, 
     uint64_t comps = 0;
     for (auto &t : cts) comps += t.r;
     if (!wpp) wpp = (uint32_t)dev::waves_per_poly(c.p.N);
-    return pack_tasks(cts, gw, wpp, spread_cap(d, comps, gw, wpp));
+    // whole rounds of full groups on every compute unit first; what is left spreads as a
+    // batch of its own (half-full groups take 0.6 of a full group's time: 7.4 against 12.8 ms
+    // for 630 steps at N = 1024)
+    const uint64_t round = (uint64_t)(gw / wpp) * (uint64_t)d.num_cu, full = comps / round * round;
+    return pack_tasks(cts, gw, wpp, spread_cap(d, comps - full, gw, wpp), full);
 }
 
 // Valid ids; returns how many name general (two-bootstrap) tables.
@@ -379,6 +472,24 @@ static dev::WaveTask *upload_tasks(Device &d, const std::vector<dev::WaveTask> &
     return dt;
 }
 
+dev::MxArgs mx_args(const mm_ctx &c, const Device &d)
+{
+    dev::MxArgs X{};
+    if (!d.mx_cst) return X;
+    const mm_params &p = c.p;
+    uint32_t goff = 0;
+    for (uint32_t u = 0; u < p.l; u++) goff += (1u << (p.log2_B - 1)) << (u * p.log2_B);
+    X.cst = (const int32_t *)d.mx_cst;
+    X.bsk = (const int32_t *)d.mx_bsk;
+    X.bal64 = (int64_t)((uint64_t)0x80808080u << 32);
+    X.field = (goff << c.sg) - (p.Q - 1) / 2 + (c.sg ? 1u << (c.sg - 1) : 0u);
+    X.bias = (128u - (1u << (p.log2_B - 1))) * 0x01010101u;
+    X.two16 = 65536;
+    X.two32 = centred(to_mont(1, p.Q), p.Q);
+    X.num_cu = (uint32_t)d.num_cu;
+    return X;
+}
+
 dev::BrArgs br_args(const mm_ctx &c, const Device &d)
 {
     dev::BrArgs A{};
@@ -397,6 +508,7 @@ dev::BrArgs br_args(const mm_ctx &c, const Device &d)
     A.twf = d.twf;
     A.twi = d.twi;
     A.tv = d.tv;
+    A.mx = mx_args(c, d);
     return A;
 }
 
@@ -646,6 +758,11 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     // per compute unit, two digit groups per component (6.5 against 7.4 ms for one
     // ciphertext, 12.2 against 12.7 ms for 512 components; 20.3 against 18.2 ms at 1024)
     const uint64_t comps = sum_r(c, ids, count), cu = (uint64_t)d.num_cu;
+    // where the matrix-core kernel applies: the fused shape with one wave per component above
+    // one component per compute unit (630 steps take 7.4 to 7.9 ms for 8 to 1024 components,
+    // 12.8 for 2048, 102 for 16,384), up to that the two digit groups (6.4 ms for 4
+    // components, 7.5 for 148, 12.2 for 512)
+    if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};
     const bool two_wave = wide_slots_ok(c, ids, count);
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
         (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
@@ -801,6 +918,7 @@ dev::WideArgs wide_args(const mm_ctx &c, const Device &d)
     A.twf1 = d.twf2;
     A.twi1 = d.twi2;
     A.tv = d.tv;
+    A.mx = mx_args(c, d);
     return A;
 }
 

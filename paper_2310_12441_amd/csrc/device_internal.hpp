@@ -44,6 +44,7 @@ struct Device {
     uint32_t *bsk = nullptr, *bsk_corr = nullptr, *ksk = nullptr, *twf = nullptr, *twi = nullptr, *tv = nullptr;
     uint32_t *twf2 = nullptr, *twi2 = nullptr, qn2 = 0;  // second prime of a wide ring modulus
     uint32_t *twf_sub = nullptr, *twi_sub = nullptr;     // split rings: per-sub-ring twiddles
+    uint32_t *mx_cst = nullptr, *mx_bsk = nullptr;       // the matrix-core step: constants, key in its order
     size_t tv_words = 0, tables_uploaded = 0;
     DevBuf ws[WS_COUNT];
     PinBuf pin[2];
@@ -72,7 +73,7 @@ struct Device {
             if (b.ev) hipEventDestroy(b.ev);
         }
         for (void *p : {(void *)bsk, (void *)bsk_corr, (void *)ksk, (void *)twf, (void *)twi, (void *)tv,
-                        (void *)twf2, (void *)twi2, (void *)twf_sub, (void *)twi_sub})
+                        (void *)twf2, (void *)twi2, (void *)twf_sub, (void *)twi_sub, (void *)mx_cst, (void *)mx_bsk})
             if (p) hipFree(p);
         for (auto &e : tev)
             if (e) hipEventDestroy(e);
@@ -108,7 +109,8 @@ struct Sched {
 };
 
 std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uint32_t gw, uint32_t wpp,
-                                      uint32_t cap = 0);
+                                      uint32_t cap = 0, uint64_t full = 0);
+dev::MxArgs mx_args(const mm_ctx &c, const Device &d);
 uint32_t spread_cap(const Device &d, uint64_t comps, uint32_t gw, uint32_t wpp);
 KsSched ks_default(const mm_ctx &c, const Device &d, size_t count);
 size_t ks_part_words(const mm_ctx &c, const KsSched &k, size_t count);

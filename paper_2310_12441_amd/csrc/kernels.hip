@@ -16,6 +16,7 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "rotation_common.hpp"
 
 namespace mm {
 namespace dev {
@@ -27,46 +28,11 @@ __host__ __device__ constexpr uint32_t gadget_offset(uint32_t log2B, uint32_t l)
     return off;
 }
 
-__device__ __forceinline__ uint32_t modswitch_dev(uint32_t x, uint32_t q_from, uint32_t q_to)
-{
-    if (q_from == q_to) return x;
-    const uint64_t num = 2ull * (uint64_t)x * q_to + q_from;
-    return (uint32_t)((num / (2ull * q_from)) % q_to);
-}
-
 __global__ void k_modswitch(const uint32_t *__restrict__ in, uint32_t *__restrict__ out, size_t count,
                             uint32_t q_from, uint32_t q_to)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
         out[i] = modswitch_dev(in[i], q_from, q_to);
-}
-
-// Row j of Phi(c), c = a r + b: source component (j - b) mod r and monomial
-// exponent a + [j < b] (eq. ex1:BPc).
-__device__ __forceinline__ void phi_row(uint32_t c, uint32_t r, uint32_t j, uint32_t &src, uint32_t &e)
-{
-    const uint32_t a = c / r, b = c - a * r;
-    src = (j + r - b) % r;
-    e = a + (j < b ? 1u : 0u);
-}
-
-// A wave's task, every field moved to scalar registers (the same for all lanes),
-// so that the step index, key and ciphertext addresses derived from it stay
-// scalar and the per-lane part of each address is one 32-bit offset.
-__device__ __forceinline__ WaveTask uniform_task(const WaveTask &t)
-{
-    WaveTask u;
-    u.ct = __builtin_amdgcn_readfirstlane(t.ct);
-    u.comp = __builtin_amdgcn_readfirstlane(t.comp);
-    u.r = __builtin_amdgcn_readfirstlane(t.r);
-    u.tv_off = __builtin_amdgcn_readfirstlane(t.tv_off);
-    u.q_in = __builtin_amdgcn_readfirstlane(t.q_in);
-    u.i0 = __builtin_amdgcn_readfirstlane(t.i0);
-    u.flags = __builtin_amdgcn_readfirstlane(t.flags);
-    u.steps = __builtin_amdgcn_readfirstlane(t.steps);
-    u.acc_off = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(t.acc_off >> 32)) << 32) |
-                __builtin_amdgcn_readfirstlane((uint32_t)t.acc_off);
-    return u;
 }
 
 // LDS per component slot: two accumulator buffers, each a swizzled pair (a, b).
@@ -792,6 +758,10 @@ static void launch_br_n(const BrArgs &A, int gw, int grid, hipStream_t st, int w
 
 void launch_blind_rotate(uint32_t N, const BrArgs &A, int gw, int grid, hipStream_t st, int wpp, int ntt)
 {
+    if (A.mx.cst && gw == 8 && (wpp == 0 || wpp == 1) && ntt == 0) {
+        launch_mx_rotate(A, grid, st);
+        return;
+    }
     switch (N) {
     case 256: launch_br_n<256>(A, gw, grid, st, wpp, ntt); break;
     case 512: launch_br_n<512>(A, gw, grid, st, wpp, ntt); break;

@@ -31,6 +31,21 @@ struct WaveTask {
     uint64_t acc_off;  // word offset of the ciphertext's accumulator state (r x 2 x N)
 };
 
+// The matrix-core kernels (kernels_mx.hip): N = 1024, one prime, digits of at most 7 bits.
+constexpr uint32_t MX_CONST_WORDS = (36 * 64 + 16) * 4;  // words of the constant block
+constexpr uint32_t MX_MAX_L = 4;                         // gadget length their LDS holds
+
+struct MxArgs {
+    const int32_t *cst;  // constant operands, twiddles and row factors, MX_CONST_WORDS (null: do not apply)
+    const int32_t *bsk;  // [n][keys][2l][2][N] in these kernels' order, x 2^64 / N, balanced
+    int64_t bal64;       // 0x80808080 2^32: the bias of a reduction whose result is cut into balanced bytes
+    uint32_t field;      // (offset of the digit fields) 2^sg - (Q - 1) / 2 + 2^(sg - 1)
+    uint32_t bias;       // (128 - B/2) in every byte: a digit field plus this, xor 128, is the signed digit
+    int32_t two16;       // 65536, as an argument so that the compiler keeps the 64-bit multiply-add
+    int32_t two32;       // 2^32 mod Q, balanced
+    uint32_t num_cu;     // compute units
+};
+
 struct BrArgs {
     const WaveTask *tasks;
     int num_groups;
@@ -45,6 +60,7 @@ struct BrArgs {
     const uint32_t *tv;        // test-vector arena
     uint32_t *acc_state;       // accumulators carried between launches
     uint32_t *ext_out;         // [ct][N + 1] extracted samples
+    MxArgs mx;                 // the matrix-core kernels (cst null where they do not apply)
 };
 
 // One (ciphertext, component) pair of the wide-modulus blind rotation: a
@@ -84,7 +100,9 @@ struct WideArgs {
     uint32_t *outb;            // products after the inverse stages within sub-rings, [task][part][N]
     const uint32_t *twf_sub;   // [M][SPLIT_NS]: the forward twiddles of each sub-ring's remaining stages
     const uint32_t *twi_sub;   // [M][SPLIT_NS]: the same for the inverse
+    MxArgs mx;                 // the matrix-core kernels (cst null where they do not apply)
 };
+
 
 // Sub-ring size of the split blind rotation: rings of 16384 coefficients and
 // more run their NTT stages that mix sub-rings in separate kernels through
@@ -146,6 +164,12 @@ void launch_wide_init(uint32_t N, int npr, const WideArgs &A, uint32_t num_tasks
 // ps (two primes): one workgroup per component and prime (dg = 2 too: N = 1024, 2048).
 void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st,
                       int wpp = 0, int dg = 1, bool ps = false);
+// The blind rotation and one CMux step on the matrix cores.
+void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st);
+void launch_mx_step(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
+// polys polynomials of the NTT-domain key (bit-reversed, x 2^32 / N) into the order and scale of MxArgs::bsk
+void launch_mx_keys(const uint32_t *src, uint32_t *dst, size_t polys, uint32_t Q, uint32_t qn, uint32_t two64,
+                    hipStream_t st);
 bool wide_supports_wpp(uint32_t N, int npr, int wpp);
 bool wide_supports_dg(uint32_t N, int npr, int wpp);  // two digit groups of wpp waves
 bool wide_supports_ps(uint32_t N, int npr, int dg = 1);  // one workgroup per prime (of dg digit groups)

@@ -35,43 +35,10 @@
 
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "rotation_common.hpp"
 
 namespace mm {
 namespace dev {
-
-// a' = round(x M / q) (Sec. 2 item (9)), ties upward.
-__device__ __forceinline__ uint32_t wide_modswitch(uint32_t x, uint32_t q, uint32_t M)
-{
-    return (uint32_t)(((2ull * x * M + q) / (2ull * q)) % M);
-}
-
-// Row j of Phi(c) for c = a r + b (eq. ex1:BPc): source component (j - b) mod r
-// and monomial x^(a + [j < b]), returned as a shift e in [0, N) and a sign.
-struct WideRow {
-    uint32_t src, e;
-    bool neg;
-};
-
-__device__ __forceinline__ WideRow wide_row(uint32_t c, uint32_t r, uint32_t j, uint32_t N)
-{
-    const uint32_t a = c / r, b = c - a * r;
-    WideRow w;
-    w.src = j >= b ? j - b : j + r - b;
-    uint32_t e = (a + (j < b ? 1u : 0u)) % (2 * N);
-    w.neg = e >= N;
-    w.e = w.neg ? e - N : e;
-    return w;
-}
-
-// Coefficient idx of x^e p (negacyclic, e < N): p[idx - e], negated when the
-// index wraps; `neg` folds in a further x^N = -1.
-__device__ __forceinline__ uint32_t wide_rot_load(const uint32_t *p, uint32_t idx, const WideRow &w, uint32_t N,
-                                                  uint32_t Q)
-{
-    const uint32_t v = p[(idx - w.e) & (N - 1)];
-    const bool flip = (idx < w.e) != w.neg;
-    return (flip && v) ? Q - v : v;
-}
 
 template <int N, int NPR>
 __global__ __launch_bounds__(256) void k_wide_init(WideArgs A)
@@ -101,16 +68,6 @@ __global__ __launch_bounds__(256) void k_wide_init(WideArgs A)
 // At N >= 8192 (one prime only) 16 coefficients per lane: N / 1024 waves, 16
 // at N = 16384, the most one workgroup holds.
 constexpr int wide_wpp(int N) { return N > 4096 ? N / 1024 : (N > 512 ? N / 512 : 1); }
-
-// Work item of workgroup b of a grid of g: the hardware deals workgroups to the eight
-// XCDs in turn (b mod 8), each with its own L2; this mapping gives each XCD a contiguous
-// eighth of the items (the rest, g mod 8, in order), so the components of one
-// ciphertext -- which read each other's accumulators through the rotation -- share an L2.
-__device__ __forceinline__ uint32_t xcd_item(uint32_t b, uint32_t g)
-{
-    const uint32_t full = g / 8 * 8;
-    return b < full ? (b % 8) * (full / 8) + b / 8 : b;
-}
 
 // Waves per EU the compiler is asked to leave room for: three (measured best at
 // N = 2048), or what a workgroup of 16 waves leaves anyway.
@@ -671,6 +628,10 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
             WIDE_DISPATCH(N, 2, P_)
 #undef P_
         }
+        return;
+    }
+    if (npr == 1 && N == 1024 && A.mx.cst && dg == 1) {
+        launch_mx_step(keys, A, num_tasks, st);
         return;
     }
     if (dg == 2 && npr == 1 && N == 1024 && wpp == 4) {

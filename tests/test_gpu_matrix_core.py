@@ -1,0 +1,111 @@
+"""The blind rotation on the matrix cores (N = 1024, digits of at most 7 bits), exact
+against the oracle: every gadget length and digit width at the edges of its range, both
+secrets, r from 1 to 8 in groups with idle component slots, one CMux step and many, and
+keys whose NTT values all sit at the largest magnitude a residue can have."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import oracle
+from synth import Params, enc_draws, key_draws, messages, negacyclic_table
+
+pytestmark = pytest.mark.gpu
+N = 1024
+
+
+def _binding():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2310_12441_amd import binding
+    return binding
+
+
+def _context(p, seed, draws=None):
+    draws = draws or key_draws(p, seed)
+    ctx = _binding().Context(p, draws)
+    ctx.device_init(0)
+    return ctx, oracle.KeySet(p, draws)
+
+
+def _fused(ctx, ids):
+    """Pin the fused shape with one wave per component, lockstep schedule."""
+    for k in range(ctx.schedule_count(ids)):
+        d = ctx.schedule_describe(ids, k)
+        if d[0] == 8 and d[3] == 1 and d[5] == 0:
+            return ctx.set_schedule(ids, k)
+    raise AssertionError("no fused schedule")
+
+
+@pytest.mark.parametrize("l,log2_B,ternary,Q", [(1, 7, False, 0), (2, 7, True, 0), (3, 7, False, 0), (4, 7, True, 0),
+                                                (4, 1, False, 0), (4, 5, True, 0), (4, 7, False, 12289),
+                                                (4, 6, False, 1073692673)])
+def test_fused_steps_and_bootstrap(l, log2_B, ternary, Q):
+    p = replace(Params(n=6, N=N, log2_B=log2_B, l=l), ternary=ternary)
+    if Q:
+        p = replace(p, Q=Q)
+    ctx, keys = _context(p, 2100 + 10 * l + log2_B)
+    ids, cts, Vs, rs = [], [], [], []
+    for k, r in enumerate((1, 8, 3, 2, 5)):
+        t = 64
+        f = negacyclic_table(t, 64, 60 + k)
+        tid = ctx.table_create(t, 64, r, f, 2 * N * r if r in (1, 2, 8) else 12289)
+        q = 2 * N * r if r in (1, 2, 8) else 12289
+        ed = enc_draws(p.n, q, 1, 70 + k)
+        ids.append(tid)
+        cts.append(oracle.encrypt(p.n, q, t, keys.s, messages(t, 1, 80 + k), ed["a"], ed["e"])[0])
+        Vs.append(oracle.test_vector(N, r, p.Q, t, 64, f))
+        rs.append((r, q))
+    print("matrix core l", l, "log2_B", log2_B, "ternary", ternary, "Q", p.Q, flush=True)
+    for steps in (1, p.n):
+        got, off = ctx.blind_rotate(ids, np.array(cts), steps), 0
+        for j, (r, q) in enumerate(rs):
+            size = r * 2 * N
+            want = oracle.blind_rotate(p, r, keys.bsk, Vs[j], oracle.modswitch(cts[j], q, 2 * N * r), steps)
+            np.testing.assert_array_equal(got[off:off + size].reshape(r, 2, N), want, err_msg=f"r {r} steps {steps}")
+            off += size
+    _fused(ctx, ids)
+    out = ctx.bootstrap(ids, np.array(cts), q_out=p.Q)
+    for j, (r, q) in enumerate(rs):
+        np.testing.assert_array_equal(out[j], oracle.bootstrap(p, r, keys.bsk, keys.ksk, Vs[j], q, p.Q, cts[j]))
+    ctx.close()
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+def test_largest_key_magnitude(sign):
+    """Masks a(x) = c with c 2^64 / N = +-(Q - 1) / 2: every NTT value the products read on that
+    side is the largest balanced residue, so the 64-bit sums come as near their bound as keys can
+    bring them."""
+    p = Params(n=3, N=N, log2_B=7, l=4)
+    draws = key_draws(p, 2200)
+    c = sign * (p.Q - 1) // 2 * N * pow(pow(2, 64, p.Q), p.Q - 2, p.Q) % p.Q
+    draws["bsk_a"] = np.zeros_like(draws["bsk_a"])
+    draws["bsk_a"][:, :, 0] = c
+    ctx, keys = _context(p, 0, draws)
+    r, t = 4, 64
+    f = negacyclic_table(t, 64, 61)
+    tid = ctx.table_create(t, 64, r, f)
+    V = oracle.test_vector(N, r, p.Q, t, 64, f)
+    ed = enc_draws(p.n, 2 * N * r, 2, 71)
+    ct = oracle.encrypt(p.n, 2 * N * r, t, keys.s, messages(t, 2, 81), ed["a"], ed["e"])
+    got = ctx.blind_rotate([tid] * 2, ct, 3).reshape(2, r, 2, N)
+    for j in range(2):
+        np.testing.assert_array_equal(got[j], oracle.blind_rotate(p, r, keys.bsk, V, ct[j], 3))
+    ctx.close()
+
+
+@pytest.mark.parametrize("count", [257, 513, 700])
+def test_rounds_with_a_thin_tail(count):
+    """Batches whose last round of groups is spread over all compute units equal the same
+    ciphertexts one by one (r = 8: one ciphertext per full group, so 256 fill a round)."""
+    p = Params(n=5, N=N, log2_B=7, l=4)
+    ctx, keys = _context(p, 2300)
+    tabs = [(r, ctx.table_create(64, 64, r, negacyclic_table(64, 64, 90 + r))) for r in (8, 1, 4)]
+    pick = [tabs[0] if j < 256 else tabs[j % 3] for j in range(count)]
+    cts = np.array([oracle.encrypt(p.n, 2 * N * r, 64, keys.s, messages(64, 1, j), *(lambda e: (e["a"], e["e"]))(
+        enc_draws(p.n, 2 * N * r, 1, j)))[0] for j, (r, _) in enumerate(pick)])
+    ids = np.array([tid for _, tid in pick], np.int32)
+    _fused(ctx, ids)
+    np.testing.assert_array_equal(ctx.bootstrap(ids, cts), ctx.bootstrap(ids, cts, plain=True))
+    ctx.close()
