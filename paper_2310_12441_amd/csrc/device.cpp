@@ -126,25 +126,108 @@ static uint32_t balanced_byte(int32_t x, int j)
     return ((((uint32_t)x + 0x80808080u) ^ 0x80808080u) >> (8 * j)) & 255u;
 }
 
-// The matrix-core step exists for N = 1024 at the 31-bit modulus with digits whose
-// balanced value fits a signed byte (fields up to B, minus B/2: B <= 2^7), and where
-// the 64-bit sums of a key's 2l products stay below 2^63 with the folded sums of the
+// The matrix-core kernels exist for some rings (mx_supports) with digits whose balanced value
+// fits a signed byte (fields up to B, minus B/2: B <= 2^7), or two with two primes (B <= 2^15;
+// the second prime below 2^24),
+// and where the 64-bit sums of a key's 2l products stay below 2^63 with the folded sums of the
 // key before.  Products: |X| <= Q/2 + 2^13, |K| <= Q/2; fold: 2^31 |2^32 mod Q| + 2^32.
 static bool mx_applies(const mm_ctx &c)
 {
     const mm_params &p = c.p;
-    if (c.wide || p.N != 1024 || p.log2_B > 7 || p.l > dev::MX_MAX_L) return false;
-    const unsigned __int128 half = p.Q / 2, two32 = (unsigned)std::abs(centred(to_mont(1, p.Q), p.Q));
-    const unsigned __int128 sums = (unsigned __int128)(2 * p.l) * (half + 8192 + 1) * half;
-    const unsigned __int128 fold = c.keys == 2 ? ((unsigned __int128)two32 << 31) + ((unsigned __int128)1 << 32) : 0;
-    return sums + fold < ((unsigned __int128)1 << 63);
+    if (!dev::mx_supports(p.N, c.wide ? 2 : 1) || p.log2_B > (c.wide ? 15u : 7u) || p.l > dev::MX_MAX_L) return false;
+    if (c.wide && (p.Q2 - 1) / 2 > 0x7f7f7fu) return false;  // three limbs: |x| <= Q2 / 2 in three balanced bytes
+    for (uint32_t Q : {p.Q, c.wide ? p.Q2 : p.Q}) {
+        const unsigned __int128 half = Q / 2, two32 = (unsigned)std::abs(centred(to_mont(1, Q), Q));
+        const unsigned __int128 sums = (unsigned __int128)(2 * p.l) * (half + 8192 + 1) * half;
+        const unsigned __int128 fold = c.keys == 2 ? ((unsigned __int128)two32 << 31) + ((unsigned __int128)1 << 32) : 0;
+        if (sums + fold >= ((unsigned __int128)1 << 63)) return false;
+    }
+    return true;
 }
 
-// The constant block of kernels_mx.hip.  An operand is 64 lanes x 16 bytes: byte b of
+// The constant block of two primes, N = 2048 (MxWide in kernels_mx.hip).  Empty where a limb's
+// sum could leave 32 bits once joined to the next one (128 times a row's bytes, times 257): the
+// kernels then do not apply.
+static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
+{
+    const uint32_t N = c.p.N, T1 = 2, D = 2, NB = T1 * D;
+    std::vector<uint32_t> out(dev::MX_WIDE_CONST_WORDS, 0);
+    bool fits = true;
+    for (uint32_t pr = 0; pr < D; pr++) {
+        const NttTables &T = pr ? c.ntt2 : c.ntt;
+        const uint32_t Q = T.Q, nl = pr ? 3 : 4, ia = 8 * T1;
+        const uint32_t fb = T1 * NB * nl, twf = fb + 4 * nl;
+        auto ops = [&](uint32_t n) { return T1 * NB * n + 4 * n + 8 * T1; };  // of a prime in LDS
+        std::vector<uint32_t> pw(2 * N);
+        pw[0] = 1;
+        for (uint32_t k = 1; k < 2 * N; k++) pw[k] = mulmod(pw[k - 1], T.psi, Q);
+        auto at = [&](int64_t e) { return pw[(size_t)(((e % (2 * (int64_t)N)) + 2 * N) % (2 * N))]; };
+        const size_t lds = (size_t)pr * ops(4) * 256;
+        const size_t mem = ((size_t)ops(4) + ops(3) + pr * (ia + 16 * T1 * T1)) * 256;
+        std::vector<uint64_t> sums;  // per limb of one output: the sum of the constant's bytes
+        // the four limbs of w 2^(8 m), byte b of a lane of operands at + 256 j
+        auto put = [&](size_t at_op, uint32_t lane, uint32_t b, uint32_t w, uint32_t m) {
+            const int32_t v = centred(mulmod(w, (uint32_t)((1ull << (8 * m)) % Q), Q), Q);
+            for (uint32_t j = 0; j < nl; j++) {
+                const uint32_t byte = balanced_byte(v, j);
+                out[at_op + ((size_t)j * 64 + lane) * 4 + b / 4] |= byte << (8 * (b % 4));
+                sums[j] += (uint64_t)std::abs((int)(int8_t)byte);
+            }
+        };
+        auto word = [&](size_t at_op, uint32_t lane, uint32_t s, uint32_t w) {  // w and 2^16 w, Montgomery form
+            const uint32_t f = to_mont(w, Q);
+            out[at_op + lane * 4 + s] = (uint32_t)centred(f, Q);
+            out[at_op + 256 + lane * 4 + s] = (uint32_t)centred(mulmod(f, 65536 % Q, Q), Q);
+        };
+        auto bounded = [&] {
+            for (uint64_t v : sums) fits = fits && v * 128 * 257 < (1ull << 31);
+            sums.assign(4, 0);
+        };
+        sums.assign(4, 0);
+        for (uint32_t col = 0; col < 32; col++) {
+            for (uint32_t tile = 0; tile < T1; tile++) {
+                const int64_t k1 = 32 * tile + col;
+                // first stage: digits of coefficient 32 i1 + i2, D bytes each, for output k1
+                for (uint32_t i1 = 0; i1 < 32 * T1; i1++)
+                    for (uint32_t m = 0; m < D; m++) {
+                        const uint32_t per = 32 / D, b = i1 / per, h = i1 % per / (16 / D), e = i1 % (16 / D);
+                        put(lds + (tile * NB + b) * nl * 256, col + 32 * h, D * e + m, at(32 * (int64_t)i1 * (2 * k1 + 1)), m);
+                    }
+                bounded();
+                // last stage: values k1' (tile ti, row) for output i1 = k1
+                for (uint32_t ti = 0; ti < T1; ti++)
+                    for (uint32_t row = 0; row < 32; row++)
+                        for (uint32_t m = 0; m < 4; m++) {
+                            const int64_t kk = 32 * ti + row;
+                            put(mem + (ia + ((tile * T1 + ti) * 4 + row / 8) * nl) * 256, col + 32 * (row / 4 % 2),
+                                4 * (row % 4) + m, at(-32 * k1 * (2 * kk + 1)), m);
+                        }
+                bounded();
+                for (int64_t row = 0; row < 32; row++) {
+                    const uint32_t q = (uint32_t)row / 8, lane = col + 32 * ((uint32_t)row / 4 % 2), s = (uint32_t)row % 4;
+                    // value (i2 = row, k1) forward; (k1' = 32 tile + row, i2 = col) inverse
+                    word(lds + (twf + 8 * tile + 2 * q) * 256, lane, s, at(row * (2 * k1 + 1)));
+                    word(mem + (8 * tile + 2 * q) * 256, lane, s, at(-(int64_t)col * (2 * (32 * tile + row) + 1)));
+                }
+            }
+            // second stage: w^(row col), w = psi^(2 N / 32)
+            for (int64_t row = 0; row < 32; row++)
+                for (uint32_t m = 0; m < 4; m++)
+                    put(lds + (fb + (uint32_t)row / 8 * nl) * 256, col + 32 * ((uint32_t)row / 4 % 2),
+                        4 * ((uint32_t)row % 4) + m, at((int64_t)(N / 16) * row * col), m);
+            bounded();
+        }
+    }
+    if (!fits) out.clear();
+    return out;
+}
+
+// The constant block of kernels_mx.hip for N = 1024.  An operand is 64 lanes x 16 bytes: byte b of
 // lane (c, h) belongs to column (or row) c of the constant and to contraction index
 // 16 h + b of the 32 of one instruction; twiddles are words.
 static std::vector<uint32_t> mx_tables(const mm_ctx &c)
 {
+    if (c.wide) return mx_wide_tables(c);
     const uint32_t Q = c.p.Q, N = 1024, psi = c.ntt.psi;
     std::vector<uint32_t> pw(2 * N), out(dev::MX_CONST_WORDS, 0);
     pw[0] = 1;
@@ -264,14 +347,19 @@ void device_init(mm_ctx &c, int id)
     }
     upload(&d->bsk, kb.data(), kb.size());
     upload(&d->bsk_corr, corr.data(), corr.size());
-    if (mx_applies(c)) {
-        const std::vector<uint32_t> cst = mx_tables(c);
+    const std::vector<uint32_t> cst = mx_applies(c) ? mx_tables(c) : std::vector<uint32_t>{};
+    if (!cst.empty()) {
         upload(&d->mx_cst, cst.data(), cst.size());
         if (hipMalloc((void **)&d->mx_bsk, kb.size() * 4) != hipSuccess) {
             d->mx_bsk = nullptr;
             throw Error(MM_ENOMEM, "device key allocation failed");
         }
-        dev::launch_mx_keys(d->bsk, d->mx_bsk, kb.size() / N, Q, d->qn, to_mont(to_mont(1, Q), Q), nullptr);
+        const uint32_t primes = c.wide ? 2 : 1, block = 2 * p.l * 2;
+        for (uint32_t pr = 0; pr < primes; pr++) {
+            const uint32_t Qp = pr ? p.Q2 : Q;
+            dev::launch_mx_keys(N, d->bsk, d->mx_bsk, kb.size() / N / primes, Qp, pr ? d->qn2 : d->qn,
+                                to_mont(to_mont(1, Qp), Qp), block, primes, pr, nullptr);
+        }
         HIPC(hipGetLastError());
         HIPC(hipDeviceSynchronize());
     }
@@ -484,8 +572,14 @@ dev::MxArgs mx_args(const mm_ctx &c, const Device &d)
     X.bal64 = (int64_t)((uint64_t)0x80808080u << 32);
     X.field = (goff << c.sg) - (p.Q - 1) / 2 + (c.sg ? 1u << (c.sg - 1) : 0u);
     X.bias = (128u - (1u << (p.log2_B - 1))) * 0x01010101u;
+    X.bias16 = 128u - (1u << (p.log2_B - 1));
     X.two16 = 65536;
-    X.two32 = centred(to_mont(1, p.Q), p.Q);
+    auto shifts = [](uint32_t Q, int32_t &two32, int32_t &two48) {
+        two32 = centred(to_mont(1, Q), Q);
+        two48 = centred(mulmod(to_mont(1, Q), 65536 % Q, Q), Q);
+    };
+    shifts(p.Q, X.two32, X.two48);
+    if (c.wide) shifts(p.Q2, X.two32_1, X.two48_1);
     X.num_cu = (uint32_t)d.num_cu;
     return X;
 }
@@ -636,10 +730,12 @@ int light_global_wpp(const mm_ctx &c)
 // components per compute unit.  Measured at the paper-margin parameters (N = 2048,
 // ternary, ms per bootstrap call, both shapes): one ciphertext 19.2 against 38.6,
 // 256 components 30.2 against 41.5, 1024 87.7 against 94.8, 4096 332.1 against
-// 335.3; 8192 669.2 against 663.2 (the shared digit fields computed twice).
+// 335.3; 8192 669.2 against 663.2 (the shared digit fields computed twice).  Where the
+// matrix-core kernel applies (it takes the other shape's place) up to one: 16 components
+// 17.6 against 26.4, 256 26.6 against 27.0, 384 35.7 against 29.8, 2400 196.6 against 138.7.
 bool prime_split(const mm_ctx &c, const Device &d, uint64_t comps)
 {
-    return c.wide && dev::wide_supports_ps(c.p.N, 2) && comps <= 16ull * (uint64_t)d.num_cu;
+    return c.wide && dev::wide_supports_ps(c.p.N, 2) && comps <= (d.mx_cst ? 1ull : 16ull) * (uint64_t)d.num_cu;
 }
 
 // Digit groups of those workgroups: two (N = 1024, 2048) while both primes' workgroups

@@ -31,8 +31,13 @@ struct WaveTask {
     uint64_t acc_off;  // word offset of the ciphertext's accumulator state (r x 2 x N)
 };
 
-// The matrix-core kernels (kernels_mx.hip): N = 1024, one prime, digits of at most 7 bits.
-constexpr uint32_t MX_CONST_WORDS = (36 * 64 + 16) * 4;  // words of the constant block
+// The matrix-core kernels (kernels_mx.hip): N = 1024 at one prime with digits of at most 7 bits,
+// N = 2048 at two primes (the second below 2^24) with digits of at most 15 bits.
+constexpr uint32_t MX_CONST_WORDS = (36 * 64 + 16) * 4;  // words of the constant block of N = 1024
+// of N = 2048, operands of 256 words: per prime the first stage's 2 x 4 blocks of four limbs
+// (three at the second prime), the second's 4 blocks, 16 of twiddles each way, the last stage's
+// 16 blocks
+constexpr uint32_t MX_WIDE_CONST_WORDS = (7 * (8 + 4 + 16) + 2 * 32) * 256;
 constexpr uint32_t MX_MAX_L = 4;                         // gadget length their LDS holds
 
 struct MxArgs {
@@ -41,8 +46,10 @@ struct MxArgs {
     int64_t bal64;       // 0x80808080 2^32: the bias of a reduction whose result is cut into balanced bytes
     uint32_t field;      // (offset of the digit fields) 2^sg - (Q - 1) / 2 + 2^(sg - 1)
     uint32_t bias;       // (128 - B/2) in every byte: a digit field plus this, xor 128, is the signed digit
+    uint32_t bias16;     // 128 - B/2: a two-byte digit field plus this, low byte xor 128, is its balanced bytes
     int32_t two16;       // 65536, as an argument so that the compiler keeps the 64-bit multiply-add
-    int32_t two32;       // 2^32 mod Q, balanced
+    int32_t two32, two48;      // 2^32 and 2^48 mod Q, balanced
+    int32_t two32_1, two48_1;  // the same for the second prime
     uint32_t num_cu;     // compute units
 };
 
@@ -166,10 +173,12 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
                       int wpp = 0, int dg = 1, bool ps = false);
 // The blind rotation and one CMux step on the matrix cores.
 void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st);
-void launch_mx_step(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
-// polys polynomials of the NTT-domain key (bit-reversed, x 2^32 / N) into the order and scale of MxArgs::bsk
-void launch_mx_keys(const uint32_t *src, uint32_t *dst, size_t polys, uint32_t Q, uint32_t qn, uint32_t two64,
-                    hipStream_t st);
+void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
+bool mx_supports(uint32_t N, int npr);
+// polys polynomials of one prime's NTT-domain key (bit-reversed, x 2^32 / N) into the order and
+// scale of MxArgs::bsk; the prime's polynomials are blocks of `block` every primes * block
+void launch_mx_keys(uint32_t N, const uint32_t *src, uint32_t *dst, size_t polys, uint32_t Q, uint32_t qn, uint32_t two64,
+                    uint32_t block, uint32_t primes, uint32_t pr, hipStream_t st);
 bool wide_supports_wpp(uint32_t N, int npr, int wpp);
 bool wide_supports_dg(uint32_t N, int npr, int wpp);  // two digit groups of wpp waves
 bool wide_supports_ps(uint32_t N, int npr, int dg = 1);  // one workgroup per prime (of dg digit groups)

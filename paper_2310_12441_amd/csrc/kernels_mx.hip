@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -70,6 +71,14 @@ static_assert((MX_VECS + 8 * 64) * 4 == (int)MX_CONST_WORDS, "constant block siz
 // Position of register v of a lane: row 8 (v / 4) + 4 half + v % 4, 32 words per row.
 __device__ __forceinline__ int mx_off(int v) { return 256 * (v / 4) + 32 * (v % 4); }
 
+// Two limb sums joined (upper: limbs 2 and 3, or limb 2 alone with NL = 3).
+template <int NL>
+__device__ __forceinline__ void mx_join(bool upper, const v16i &a, const v16i &b, int32_t (&o)[16])
+{
+#pragma unroll
+    for (int v = 0; v < 16; v++) o[v] = upper && NL == 3 ? a[v] : a[v] + (int32_t)((uint32_t)b[v] << 8);
+}
+
 // One 32-point stage on a residue polynomial given as bytes: the four limb sums of each
 // output joined to lo + 2^16 hi, two limbs at a time.  LEFT: the constant is the left
 // operand.  work(t), t = 0 .. 7, is vector arithmetic of another polynomial placed after
@@ -77,27 +86,27 @@ __device__ __forceinline__ int mx_off(int v) { return 256 * (v / 4) + 32 * (v % 
 // ALU idle and its arithmetic the matrix unit (40 matrix instructions and 480 others of
 // this mix take 3.7k clocks per wave one after the other, 3.2k interleaved, at two waves
 // per SIMD).
-template <bool LEFT, class Work>
-__device__ __forceinline__ void mx_stage(const v4i *cst, const v4i (&z)[4], int lane, int32_t (&lo)[16],
+// NL = 3: constants of at most 23 bits have three limbs, hi is the third alone (operands
+// [contraction block][NL]).
+template <bool LEFT, int NL = 4, class Work>
+__device__ __forceinline__ void mx_stage(const v4i *fb, const v4i (&z)[4], int lane, int32_t (&lo)[16],
                                          int32_t (&hi)[16], Work work)
 {
-    v4i k[2] = {cst[MX_FB * 64 + lane], cst[(MX_FB + 1) * 64 + lane]};
+    v4i k[2] = {fb[lane], fb[64 + lane]};
     v16i c[2];
 #pragma unroll
     for (int t = 0; t < 8; t++) {
-        const int q = t & 3;
+        const int q = t & 3, nj = t < 4 ? 2 : NL - 2;
         if (q == 0) c[0] = c[1] = v16i{};
 #pragma unroll
-        for (int j = 0; j < 2; j++) c[j] = LEFT ? mfma(k[j], z[q], c[j]) : mfma(z[q], k[j], c[j]);
+        for (int j = 0; j < nj; j++) c[j] = LEFT ? mfma(k[j], z[q], c[j]) : mfma(z[q], k[j], c[j]);
         if (t < 7) {
 #pragma unroll
-            for (int j = 0; j < 2; j++) k[j] = cst[(MX_FB + 4 * ((t + 1) & 3) + 2 * ((t + 1) >> 2) + j) * 64 + lane];
+            for (int j = 0; j < (t < 3 ? 2 : NL - 2); j++)
+                k[j] = fb[(NL * ((t + 1) & 3) + 2 * ((t + 1) >> 2) + j) * 64 + lane];
         }
         work(t);
-        if (q == 3) {
-#pragma unroll
-            for (int v = 0; v < 16; v++) (t == 7 ? hi : lo)[v] = c[0][v] + (int32_t)((uint32_t)c[1][v] << 8);
-        }
+        if (q == 3) mx_join<NL>(t == 7, c[0], c[1], t == 7 ? hi : lo);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -201,13 +210,29 @@ __device__ __forceinline__ void mx_products(const v4i *dig, const v4i *cst, cons
             __builtin_amdgcn_sched_barrier(0);
         }
         request(0);
-        mx_stage<true>(cst, z[0], lane, lo[0], hi[0],
+        mx_stage<true>(cst + MX_FB * 64, z[0], lane, lo[0], hi[0],
                        [&](int t) { mx_twist(t, lo[1], hi[1], cst + MX_TWF * 64 + lane, 64, X, m, s4, z[1]); });
         request(1);
-        mx_stage<true>(cst, z[1], lane, lo[1], hi[1], [&](int t) { mx_mac(t, lo[0], hi[0], k[0], X, m, r4, acc); });
+        mx_stage<true>(cst + MX_FB * 64, z[1], lane, lo[1], hi[1], [&](int t) { mx_mac(t, lo[0], hi[0], k[0], X, m, r4, acc); });
 #pragma unroll
         for (int t = 0; t < 8; t++) mx_mac(t, lo[1], hi[1], k[1], X, m, r4, acc);
     }
+}
+
+// Registers 4 q .. 4 q + 3 of one part's sums as balanced bytes of their residues x 2^-32:
+// 2^32 h + l -> h (2^32 mod Q) + l, which one reduction brings below 2^31; BAL as its bias.
+__device__ __forceinline__ void mx_cut(int q, const int64_t (&acc)[16], const MxArgs &X, const ModS &m, int64_t (&s4)[4],
+                                       v4i (&z)[4])
+{
+    int32_t o[4];
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        const uint64_t low = (uint32_t)acc[4 * q + s] | ((uint64_t)BAL << 32);
+        s4[s] = (int64_t)(int32_t)(acc[4 * q + s] >> 32) * X.two32 + (int64_t)low;
+    }
+    redc4(s4, m, o);
+#pragma unroll
+    for (int s = 0; s < 4; s++) z[q][s] = o[s] ^ (int32_t)BAL;
 }
 
 // The sums back to coefficients: out(part, v, x) with x in [0, Q).
@@ -224,18 +249,7 @@ __device__ __forceinline__ void mx_inverse(const int64_t (&acc)[2][16], const v4
 #pragma unroll
     for (int j = 0; j < 8; j++) tw[j] = reinterpret_cast<const v4i *>(X.cst)[MX_VECS + j * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);
-    auto cut = [&](int p, int q) {
-        // 2^32 h + l -> h (2^32 mod Q) + l, which one reduction brings below 2^31; BAL as its bias
-        int32_t o[4];
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            const uint64_t low = (uint32_t)acc[p][4 * q + s] | ((uint64_t)BAL << 32);
-            s4[s] = (int64_t)(int32_t)(acc[p][4 * q + s] >> 32) * X.two32 + (int64_t)low;
-        }
-        redc4(s4, m, o);
-#pragma unroll
-        for (int s = 0; s < 4; s++) z[p][q][s] = o[s] ^ (int32_t)BAL;
-    };
+    auto cut = [&](int p, int q) { mx_cut(q, acc[p], X, m, s4, z[p]); };
     auto twist = [&](int p, int t) { mx_twist(t, lo[p], hi[p], tw, 1, X, m, s4, z[p]); };
     auto last = [&](int p, int q) {
         const v4i f = cst[MX_FIN * 64 + 4 * q + 2 * (lane >> 5)], f16 = cst[MX_FIN * 64 + 4 * q + 2 * (lane >> 5) + 1];
@@ -248,10 +262,10 @@ __device__ __forceinline__ void mx_inverse(const int64_t (&acc)[2][16], const v4
     };
 #pragma unroll
     for (int q = 0; q < 4; q++) cut(0, q);
-    mx_stage<false>(cst, z[0], neg, lo[0], hi[0], [&](int t) { if (t & 1) cut(1, t >> 1); });
-    mx_stage<false>(cst, z[1], neg, lo[1], hi[1], [&](int t) { twist(0, t); });
-    mx_stage<true>(cst, z[0], neg, lo[0], hi[0], [&](int t) { twist(1, t); });
-    mx_stage<true>(cst, z[1], neg, lo[1], hi[1], [&](int t) { if (t & 1) last(0, t >> 1); });
+    mx_stage<false>(cst + MX_FB * 64, z[0], neg, lo[0], hi[0], [&](int t) { if (t & 1) cut(1, t >> 1); });
+    mx_stage<false>(cst + MX_FB * 64, z[1], neg, lo[1], hi[1], [&](int t) { twist(0, t); });
+    mx_stage<true>(cst + MX_FB * 64, z[0], neg, lo[0], hi[0], [&](int t) { twist(1, t); });
+    mx_stage<true>(cst + MX_FB * 64, z[1], neg, lo[1], hi[1], [&](int t) { if (t & 1) last(0, t >> 1); });
 #pragma unroll
     for (int q = 0; q < 4; q++) last(1, q);
 }
@@ -468,27 +482,357 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
-// The bootstrapping key in this kernel's order: dst[poly][q][lane][s], entry of
-// NTT position k = k1 + 32 k2 (k1 = lane % 32, k2 = 8 q + 4 (lane / 32) + s), from the
-// bit-reversed, Montgomery-form key, times another 2^32 and balanced.
-__global__ __launch_bounds__(256) void k_mx_keys(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst,
-                                                 uint32_t Q, uint32_t qn, uint32_t two64)
+// ------------------------------------------------------------------ two primes, N = 2048
+//
+// N = 64 x 32: the first stage contracts over i1 < 64 and its outputs k1 fall into T1 = 2 tiles
+// of 32, after which everything up to the products is local to a tile; the inverse's last
+// stage contracts over all k1 and its outputs i1 fall into two tiles again.  A wave owns one
+// tile of one prime of a component, four waves per component.  A digit (at most 15 bits)
+// is two balanced bytes; the component's waves form the digits of one part together (each
+// wave one of the four contraction blocks) in LDS, and swap tiles through LDS before the
+// last stage.
+//
+// Bound by vector issue and the chain of one wave: with a ternary secret a step of one component
+// is some 100k clocks of its four waves (eight pairs of products 47k, digits 15k, the inverse and
+// its last stage 15k), and two components share a compute unit's SIMDs.  Measured at n = 512,
+// ternary, 2400 components: 138.7 ms, against 195.6 for one butterfly workgroup per component
+// and prime.  Of that the requests in groups (the digits' words, the last stage's constants:
+// left alone the compiler waits for every few) brought 162 -> 139 ms.
+
+// Operands per prime in LDS: the first stage [tile][block][limb], the second [q][limb], the
+// forward twiddles [tile][q][w, 2^16 w]; in memory behind both primes' of them, per prime, the
+// inverse twiddles [tile][q][w, 2^16 w] and the last stage [tile out][tile in][q][limb].  The
+// second prime is below 2^24: three limbs.
+struct MxWide {
+    static constexpr int T1 = 2, N = 1024 * T1, NB = 2 * T1, WAVES = 2 * T1, COMPS = 8 / WAVES, E = 8;
+    static constexpr int fb(int nl) { return T1 * NB * nl; }
+    static constexpr int twf(int nl) { return fb(nl) + 4 * nl; }
+    static constexpr int lds_ops(int nl) { return twf(nl) + 8 * T1; }
+    static constexpr int IA = 8 * T1;  // behind the inverse twiddles
+    static constexpr int LDS_OPS = 7 * (T1 * NB + 4) + 16 * T1;  // lds_ops of both
+    static constexpr int mem(int pr) { return LDS_OPS + pr * (IA + 16 * T1 * T1); }
+    static_assert((LDS_OPS + 2 * IA + 28 * T1 * T1) * 256 == (int)MX_WIDE_CONST_WORDS, "constant block");
+};
+
+// Two digit polynomials (digits u, u + 1 of one part; their blocks at d0, d1) through both
+// forward stages and onto acc with their key rows kr[poly] (tile's [part][q][lane]).
+template <int NB, int NL>
+__device__ __forceinline__ void mx_wide_pair(const v4i *d0, const v4i *d1, const v4i *fa, const v4i *fb, const v4i *tw,
+                                              const v4i *const (&kr)[2], size_t part_stride, int lane, const MxArgs &X,
+                                              const ModS &m, int64_t (&acc)[2][16])
 {
-    constexpr int N = MXN;
-    const size_t base = (size_t)blockIdx.x * N;
+    int32_t lo[2][16], hi[2][16];
+    v4i z[2][4], k[2][2][4];
+    int64_t s4[4];
+    int32_t r4[4];
+    auto request = [&](int p) {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int o = 0; o < 2; o++) k[p][o][q] = kr[p][o * part_stride + q * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int jj = 0; jj < 2; jj++) {
+        v16i c[2][2] = {};
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            const v4i x[2] = {d0[b * 64 + lane], d1[b * 64 + lane]};
+#pragma unroll
+            for (int j = 0; j < (jj ? NL - 2 : 2); j++) {
+                const v4i w = fa[(NL * b + 2 * jj + j) * 64 + lane];
+#pragma unroll
+                for (int p = 0; p < 2; p++) c[p][j] = mfma(x[p], w, c[p][j]);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < 2; p++) mx_join<NL>(jj, c[p][0], c[p][1], jj ? hi[p] : lo[p]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; t++) mx_twist(t, lo[0], hi[0], tw + lane, 64, X, m, s4, z[0]);
+    request(0);
+    mx_stage<true, NL>(fb, z[0], lane, lo[0], hi[0], [&](int t) { mx_twist(t, lo[1], hi[1], tw + lane, 64, X, m, s4, z[1]); });
+    request(1);
+    mx_stage<true, NL>(fb, z[1], lane, lo[1], hi[1], [&](int t) { mx_mac(t, lo[0], hi[0], k[0], X, m, r4, acc); });
+#pragma unroll
+    for (int t = 0; t < 8; t++) mx_mac(t, lo[1], hi[1], k[1], X, m, r4, acc);
+}
+
+// A barrier among the waves of one component: the other components of the workgroup go
+// their own pace, so that one's digits (memory latency, vector work) run beside another's
+// products.  Every wave of the component arrives, all are resident: the wait ends.
+struct CompSync {
+    uint32_t *count;
+    uint32_t target, waves;
+    __device__ __forceinline__ void wait_for(const uint32_t *c, uint32_t t) const
+    {
+        while ((int32_t)(__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) - t) < 0)
+            __builtin_amdgcn_s_sleep(1);
+    }
+    __device__ __forceinline__ void operator()()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        target += waves;
+        wait_for(count, target);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+};
+
+// One step of the components of a workgroup for a wave of prime pr (NL limbs); constants,
+// digits (and, before the last stage, the tiles the component's waves swap) in LDS.
+template <int KEYS, int NL>
+__device__ __forceinline__ void mx_wide_run(const WideArgs &A, uint32_t num_tasks, const v4i *cst, v4i *digits,
+                                             uint32_t *arrive)
+{
+    using C = MxWide;
+    constexpr int T1 = C::T1, N = C::N, NB = C::NB, E = C::E;
+    constexpr int pr = NL == 3 ? 1 : 0;
+    constexpr size_t PW = (size_t)2 * N, CW = 2 * PW;  // words per part, per component
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 31, half = lane >> 5;
+    const int cw = wave / C::WAVES, wi = wave % C::WAVES, tile = wi % T1;
+    v4i *const dig = digits + cw * MX_MAX_L * NB * 64;
+    const v4i *const base = cst + (pr ? C::lds_ops(4) * 64 : 0), *const fb = base + C::fb(NL) * 64;
+    const v4i *const mem = reinterpret_cast<const v4i *>(A.mx.cst) + (size_t)C::mem(pr) * 64;
+    const uint32_t Q = A.Q[pr];
+    const ModS m{(int32_t)Q, A.qn[pr]};
+    MxArgs X = A.mx;
+    X.two32 = pr ? A.mx.two32_1 : A.mx.two32;
+    const int32_t two48 = pr ? A.mx.two48_1 : A.mx.two48;
+    const int neg = ((32 - lane) & 31) | (lane & 32);
+    const uint32_t pairs = (A.l + 1) / 2;
+    CompSync sync{arrive + cw, 0, C::WAVES};
+    // the second wave of a SIMD starts when the first one's first digits are written
+    if (wave >= 4) sync.wait_for(arrive + (wave - 4) / C::WAVES, 2 * C::WAVES);
+    for (uint32_t first = xcd_item(blockIdx.x, gridDim.x) * C::COMPS; first < num_tasks; first += gridDim.x * C::COMPS) {
+        const bool has = first + cw < num_tasks;
+        const WideTask &T = A.tasks[has ? first + cw : first];
+        const uint32_t i = __builtin_amdgcn_readfirstlane(T.i0) + A.step;
+        const uint32_t r = __builtin_amdgcn_readfirstlane(T.r), comp = __builtin_amdgcn_readfirstlane(T.comp);
+        const uint32_t q_in = __builtin_amdgcn_readfirstlane(T.q_in);
+        const bool active = has && i < A.n;
+        const uint32_t *const ct_acc = A.acc_rd + T.acc_off, *const own = ct_acc + (size_t)comp * CW;
+        uint32_t *const wr = A.acc_wr + T.acc_off + (size_t)comp * CW;
+        if (has && !active)  // past step n - 1: carried over
+            for (int w = wi * 64 + lane; w < (int)CW; w += 64 * C::WAVES) wr[w] = own[w];
+        const uint32_t M = 2u * N * r;
+        const uint32_t am =
+            active ? __builtin_amdgcn_readfirstlane(modswitch_dev(A.ct_in[(size_t)T.ct * A.ct_stride + i], q_in, M)) : 0u;
+        int64_t acc[2][16];
+        uint32_t touched = 0;
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[0][v] = acc[1][v] = 0;
+#pragma unroll 1
+        for (int kp = 0; kp < 2 * KEYS; kp++) {
+            const int key = kp >> 1, part = kp & 1;
+            __asm__ volatile("" ::"v"(touched));
+            sync();  // the previous digits (at first: tiles) are read
+            if (active) {
+                // element e: coefficient 32 i1 + col, i1 = 16 wi + 8 half + e
+                const WideRow w = wide_row(key == 0 ? (M - am) % M : am, r, comp, N);
+                const uint32_t *o = own + part * PW, *s = ct_acc + (size_t)w.src * CW + part * PW;
+                const uint32_t at = 32 * (16 * wi + 8 * half) + col;
+                // every word is requested before the first is used
+                uint32_t vo[2][E], vs[2][E];
+#pragma unroll
+                for (int p = 0; p < 2; p++)
+#pragma unroll
+                    for (int e = 0; e < E; e++) {
+                        vo[p][e] = o[p * N + at + 32 * e];
+                        vs[p][e] = s[p * N + ((at + 32 * e - w.e) & (N - 1))];
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+                auto flips = [&](int e) { return (at + 32 * e < w.e) != w.neg; };
+                const ModQ m1{A.Q[1], A.qn[1]};
+                const uint64_t hw = (A.Qw - 1) / 2;
+                uint64_t y[E];
+#pragma unroll
+                for (int e = 0; e < E; e++) {
+                    auto diff = [&](int p) {
+                        const uint32_t v = vs[p][e], Qp = A.Q[p];
+                        return sub_q(flips(e) && v ? Qp - v : v, vo[p][e], Qp);
+                    };
+                    const uint32_t a0 = diff(0), a1 = diff(1);
+                    // x = a0 + Q0 ((a1 - a0) Q0^-1 mod Q1), in [0, Q0 Q1)
+                    const uint64_t x = a0 + (uint64_t)A.Q[0] * mont_mul(a1 + A.crt_cq - a0, A.crt_inv, m1);
+                    int64_t xc = x > hw ? (int64_t)(x - A.Qw) : (int64_t)x;
+                    if (A.sg) xc = (xc + (1ll << (A.sg - 1))) >> A.sg;
+                    y[e] = (uint64_t)xc + A.goff;
+                }
+                for (uint32_t u = 0; u < A.l; u++) {
+                    const uint32_t sh = u * A.log2B;
+                    const uint32_t mask = u + 1 == A.l ? 0xffffu : (1u << A.log2B) - 1;
+                    v4i d;
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        // two fields, minus B/2, as two balanced bytes each: + 0x80, low byte xor 0x80
+                        const uint32_t f0 = ((uint32_t)(y[2 * g] >> sh) & mask) + A.mx.bias16;
+                        const uint32_t f1 = ((uint32_t)(y[2 * g + 1] >> sh) & mask) + A.mx.bias16;
+                        d[g] = (int32_t)(((f0 & 0xffffu) | (f1 << 16)) ^ 0x00800080u);
+                    }
+                    dig[(u * NB + wi) * 64 + lane] = d;
+                }
+                if (A.l & 1) dig[(A.l * NB + wi) * 64 + lane] = v4i{};  // the last pair's second polynomial
+            }
+            sync();  // the digits are written
+            if (active) {
+                if (kp + 1 < 2 * KEYS) {
+                    // the lines of the next digits' reads, one a lane, so that these find them in L2
+                    const WideRow w = wide_row((kp + 1) >> 1 ? am : (M - am) % M, r, comp, N);
+                    const uint32_t idx = 32 * (16 * wi + (lane & 15)) + ((lane >> 4) & 1) * N;
+                    const uint32_t at = lane < 32 ? idx : (idx & ~(uint32_t)(N - 1)) | ((idx - w.e) & (N - 1));
+                    touched = ct_acc[(lane < 32 ? comp : w.src) * CW + ((kp + 1) & 1) * PW + at];
+                }
+                // digits of a (part 0) meet rows l + u, digits of b rows u (eq. def:gsw)
+                const v4i *K = reinterpret_cast<const v4i *>(A.mx.bsk) +
+                               (((size_t)i * KEYS + key) * 2 + pr) * (A.l * N) + (size_t)(part ? 0 : A.l) * (N / 2) +
+                               tile * 256;
+#pragma unroll 1
+                for (uint32_t g = 0; g < pairs; g++) {
+                    __asm__ volatile("" ::: "memory");
+                    const uint32_t u1 = min(2 * g + 1, A.l - 1);  // (its digits are zeros where it repeats a row)
+                    const v4i *const kr[2] = {K + (size_t)(2 * g) * (N / 2), K + (size_t)u1 * (N / 2)};
+                    mx_wide_pair<NB, NL>(dig + 2 * g * NB * 64, dig + (2 * g + 1) * NB * 64, base + tile * NB * NL * 64,
+                                          fb, base + (C::twf(NL) + 8 * tile) * 64, kr, N / 4, lane, X, m, acc);
+                }
+                if (KEYS == 2 && kp == 1) mx_fold(acc, X);
+            }
+        }
+        // the sums back to coefficients: second stage and twiddles within the tile
+        int32_t lo[2][16], hi[2][16];
+        v4i z[2][4], ti[8], x0[4 * T1];
+        int64_t s4[4];
+        __asm__ volatile("" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < 8; j++) ti[j] = mem[(8 * tile + j) * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; q++) mx_cut(q, acc[0], X, m, s4, z[0]);
+        mx_stage<false, NL>(fb, z[0], neg, lo[0], hi[0],
+                            [&](int t) { if (t & 1) mx_cut(t >> 1, acc[1], X, m, s4, z[1]); });
+        mx_stage<false, NL>(fb, z[1], neg, lo[1], hi[1],
+                            [&](int t) { mx_twist(t, lo[0], hi[0], ti, 1, X, m, s4, z[0]); });
+#pragma unroll
+        for (int t = 0; t < 8; t++) mx_twist(t, lo[1], hi[1], ti, 1, X, m, s4, z[1]);
+        // the last stage over all tiles of the prime: the tiles of part 0 into registers, those
+        // of part 1 read from LDS as operands, so that both parts share each constant
+        v4i *const swap = digits + (wave - tile) * 4 * 64;
+        sync();  // the digits are read
+#pragma unroll
+        for (int q = 0; q < 4; q++) swap[(4 * tile + q) * 64 + lane] = z[0][q];
+        sync();
+#pragma unroll
+        for (int b = 0; b < 4 * T1; b++) x0[b] = swap[b * 64 + lane];
+        sync();
+#pragma unroll
+        for (int q = 0; q < 4; q++) swap[(4 * tile + q) * 64 + lane] = z[1][q];
+        sync();
+        if (!active) continue;
+        uint32_t pos = lane;  // opaque: the addresses below are not carried through the products
+        __asm__("" : "+v"(pos));
+        const v4i *const ia = mem + (C::IA + 4 * NL * T1 * tile) * 64;
+        // constants in groups of four blocks, each group requested before the one in hand is used
+        constexpr int GROUPS = 2 * T1;
+        v4i kc[2][8];
+        auto request = [&](int g) {
+            const int jj = g / T1;
+#pragma unroll
+            for (int b = 0; b < 4; b++)
+#pragma unroll
+                for (int j = 0; j < (jj ? NL - 2 : 2); j++)
+                    kc[g & 1][2 * b + j] = ia[(NL * (4 * (g % T1) + b) + 2 * jj + j) * 64 + pos];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        request(0);
+        v16i c[2][2];
+#pragma unroll
+        for (int g = 0; g < GROUPS; g++) {
+            const int jj = g / T1;
+            if (g + 1 < GROUPS) request(g + 1);
+            if (g % T1 == 0) c[0][0] = c[0][1] = c[1][0] = c[1][1] = v16i{};
+#pragma unroll
+            for (int b = 0; b < 4; b++) {
+                const v4i x1 = swap[(4 * (g % T1) + b) * 64 + lane];
+#pragma unroll
+                for (int j = 0; j < (jj ? NL - 2 : 2); j++) {
+                    c[0][j] = mfma(kc[g & 1][2 * b + j], x0[4 * (g % T1) + b], c[0][j]);
+                    c[1][j] = mfma(kc[g & 1][2 * b + j], x1, c[1][j]);
+                }
+            }
+            if (g % T1 == T1 - 1) {
+#pragma unroll
+                for (int p = 0; p < 2; p++) mx_join<NL>(jj, c[p][0], c[p][1], jj ? hi[p] : lo[p]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const uint32_t at = 128 * (pos >> 5) + (pos & 31);
+#pragma unroll
+        for (int part = 0; part < 2; part++) {
+            const uint32_t *const from = own + part * PW + pr * N + 1024 * tile;
+            uint32_t *const to = wr + part * PW + pr * N + 1024 * tile;
+            uint32_t old[16];
+#pragma unroll
+            for (int v = 0; v < 16; v++) old[v] = from[at + mx_off(v)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                int32_t o[4];
+#pragma unroll
+                for (int s = 0; s < 4; s++)
+                    s4[s] = (int64_t)lo[part][4 * q + s] * X.two32 + (int64_t)hi[part][4 * q + s] * two48;
+                redc4(s4, m, o);
+#pragma unroll
+                for (int s = 0; s < 4; s++)  // o in (-Q, Q)
+                    to[at + mx_off(4 * q + s)] = add_q(old[4 * q + s], min((uint32_t)o[s], (uint32_t)o[s] + Q), Q);
+            }
+        }
+    }
+}
+
+template <int KEYS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_wide_step(WideArgs A, uint32_t num_tasks)
+{
+    using C = MxWide;
+    __shared__ v4i cst[C::LDS_OPS * 64];
+    __shared__ v4i digits[C::COMPS * MX_MAX_L * C::NB * 64];
+    __shared__ uint32_t arrive[C::COMPS];
+    static_assert(sizeof(digits) == 8 * 4 * 64 * 16, "one part's tile per wave");
+    if (threadIdx.x < C::COMPS) arrive[threadIdx.x] = 0;
+    for (int t = threadIdx.x; t < C::LDS_OPS * 64; t += 512) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % C::WAVES >= C::T1)
+        mx_wide_run<KEYS, 3>(A, num_tasks, cst, digits, arrive);
+    else
+        mx_wide_run<KEYS, 4>(A, num_tasks, cst, digits, arrive);
+}
+
+// The bootstrapping key in these kernels' order: dst[poly][tile][q][lane][s], entry of
+// NTT position k = k1 + 32 T1 k2 (k1 = 32 tile + lane % 32, k2 = 8 q + 4 (lane / 32) + s), from
+// the bit-reversed, Montgomery-form key, times another 2^32 and balanced.  The polynomials
+// of prime pr are blocks of `block` every primes * block.
+__global__ __launch_bounds__(256) void k_mx_keys(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst, int logN,
+                                                 uint32_t Q, uint32_t qn, uint32_t two64, uint32_t block, uint32_t primes,
+                                                 uint32_t pr)
+{
+    const uint32_t N = 1u << logN, b = blockIdx.x / block;
+    const size_t base = ((size_t)(b * primes + pr) * block + blockIdx.x % block) * N;
     const ModQ m{Q, qn};
-    for (int t = threadIdx.x; t < N; t += 256) {
-        const int q = t >> 8, lane = (t >> 2) & 63, s = t & 3;
-        const uint32_t k = (lane & 31) + 32 * (8 * q + 4 * (lane >> 5) + s);
-        const uint32_t x = mont_mul(src[base + (__brev(k) >> 22)], two64, m);
+    for (uint32_t t = threadIdx.x; t < N; t += 256) {
+        const uint32_t tile = t >> 10, q = (t >> 8) & 3, lane = (t >> 2) & 63, s = t & 3;
+        const uint32_t k = 32 * tile + (lane & 31) + (N / 32) * (8 * q + 4 * (lane >> 5) + s);
+        const uint32_t x = mont_mul(src[base + (__brev(k) >> (32 - logN))], two64, m);
         dst[base + t] = x > (Q - 1) / 2 ? x - Q : x;
     }
 }
 
-void launch_mx_keys(const uint32_t *src, uint32_t *dst, size_t polys, uint32_t Q, uint32_t qn, uint32_t two64,
-                    hipStream_t st)
+void launch_mx_keys(uint32_t N, const uint32_t *src, uint32_t *dst, size_t polys, uint32_t Q, uint32_t qn, uint32_t two64,
+                    uint32_t block, uint32_t primes, uint32_t pr, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mx_keys, dim3((uint32_t)polys), dim3(256), 0, st, src, dst, Q, qn, two64);
+    int logN = 0;
+    while ((1u << logN) < N) logN++;
+    hipLaunchKernelGGL(k_mx_keys, dim3((uint32_t)polys), dim3(256), 0, st, src, dst, logN, Q, qn, two64, block, primes, pr);
 }
 
 void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st)
@@ -497,12 +841,21 @@ void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st)
     else hipLaunchKernelGGL(k_mx_rotate<1>, dim3(grid), dim3(512), 0, st, A);
 }
 
-void launch_mx_step(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st)
+void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st)
 {
+    if (npr == 2 && N == 2048) {
+        const uint32_t grid = std::min<uint32_t>((num_tasks + MxWide::COMPS - 1) / MxWide::COMPS, A.mx.num_cu);
+        if (keys == 2) hipLaunchKernelGGL(k_mx_wide_step<2>, dim3(grid), dim3(512), 0, st, A, num_tasks);
+        else hipLaunchKernelGGL(k_mx_wide_step<1>, dim3(grid), dim3(512), 0, st, A, num_tasks);
+        return;
+    }
+    if (npr != 1 || N != 1024) return;
     const uint32_t grid = std::min<uint32_t>((num_tasks + 7) / 8, A.mx.num_cu);
     if (keys == 2) hipLaunchKernelGGL(k_mx_step<2>, dim3(grid), dim3(512), 0, st, A, num_tasks);
     else hipLaunchKernelGGL(k_mx_step<1>, dim3(grid), dim3(512), 0, st, A, num_tasks);
 }
+
+bool mx_supports(uint32_t N, int npr) { return N == (npr == 2 ? 2048u : 1024u); }
 
 }  // namespace dev
 }  // namespace mm

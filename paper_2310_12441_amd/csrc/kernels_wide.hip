@@ -620,6 +620,10 @@ static void ps_launch(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipS
 void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st,
                       int wpp, int dg, bool ps)
 {
+    if (A.mx.cst && dg == 1 && !ps) {
+        launch_mx_step(N, npr, keys, A, num_tasks, st);
+        return;
+    }
     if (ps && npr == 2) {
         if (dg == 2 && N == 1024) ps_launch<1024, 2, 2>(keys, A, num_tasks, st);
         else if (dg == 2 && N == 2048) ps_launch<2048, 2, 2>(keys, A, num_tasks, st);
@@ -628,10 +632,6 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
             WIDE_DISPATCH(N, 2, P_)
 #undef P_
         }
-        return;
-    }
-    if (npr == 1 && N == 1024 && A.mx.cst && dg == 1) {
-        launch_mx_step(keys, A, num_tasks, st);
         return;
     }
     if (dg == 2 && npr == 1 && N == 1024 && wpp == 4) {

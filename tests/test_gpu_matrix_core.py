@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
-from synth import Params, enc_draws, key_draws, messages, negacyclic_table
+from synth import Q2_DEFAULT, Params, enc_draws, key_draws, messages, negacyclic_table
 
 pytestmark = pytest.mark.gpu
 N = 1024
@@ -108,4 +108,39 @@ def test_rounds_with_a_thin_tail(count):
     ids = np.array([tid for _, tid in pick], np.int32)
     _fused(ctx, ids)
     np.testing.assert_array_equal(ctx.bootstrap(ids, cts), ctx.bootstrap(ids, cts, plain=True))
+    ctx.close()
+
+
+@pytest.mark.parametrize("l,log2_B,ternary", [(4, 15, False), (4, 15, True), (3, 15, True), (1, 15, False), (2, 7, False),
+                                              (4, 1, True)])
+def test_two_primes_2048(l, log2_B, ternary):
+    """The 54-bit ring modulus at N = 2048: odd and even gadget lengths, digit widths at both
+    ends, r from 1 to 3 with an odd number of components (a workgroup holds two), against the
+    oracle's uint64 statement; then a batch of more components than one round of workgroups
+    holds equals its ciphertexts in other shapes."""
+    p = Params(n=4, N=2048, log2_B=log2_B, l=l, Q2=Q2_DEFAULT, ternary=ternary)
+    draws = key_draws(p, 2400 + 10 * l + log2_B)
+    ctx, keys = _binding().Context(p, draws), oracle.KeySetWide(p, draws)
+    ctx.device_init(0)
+    print("two primes l", l, "log2_B", log2_B, "ternary", ternary, flush=True)
+    ids, cts, Vs, rs = [], [], [], []
+    for k, r in enumerate((1, 3, 1)):
+        f = negacyclic_table(32, 32, 60 + k)
+        q = 2 * 2048 * r
+        ed = enc_draws(p.n, q, 1, 70 + k)
+        ids.append(ctx.table_create(32, 32, r, f))
+        cts.append(oracle.encrypt(p.n, q, 32, keys.s, messages(32, 1, 80 + k), ed["a"], ed["e"])[0])
+        Vs.append(oracle.w_test_vector(2048, r, p.Q_ring, 32, 32, f))
+        rs.append(r)
+    got, off = ctx.blind_rotate(ids, np.array(cts), p.n), 0
+    for r, V, ct in zip(rs, Vs, cts):
+        np.testing.assert_array_equal(got[off:off + r * 4096].reshape(r, 2, 2048),
+                                      oracle.w_blind_rotate(p, r, keys.bsk, V, ct, p.n), err_msg=f"r {r}")
+        off += r * 4096
+    ids, cts = np.array([ids[j % 3] for j in range(601)], np.int32), np.array([cts[j % 3] for j in range(601)])
+    shapes = {ctx.schedule_describe(ids, k)[5]: k for k in reversed(range(ctx.schedule_count(ids)))}
+    ctx.set_schedule(ids, shapes[0])
+    out = ctx.bootstrap(ids, cts)
+    ctx.set_schedule(ids, shapes[5])
+    np.testing.assert_array_equal(ctx.bootstrap(ids, cts), out)
     ctx.close()
