@@ -756,6 +756,12 @@ int light_global_dg(const mm_ctx &c, const Device &d, uint64_t comps)
     return w2 && dev::wide_supports_dg(c.p.N, primes_of(c), w2) && comps <= 2ull * (uint64_t)d.num_cu ? 2 : 1;
 }
 
+// The matrix-core kernel with two waves per component: see schedule_for.
+bool mx_two_waves(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r)
+{
+    return d.mx_cst && !c.wide && max_r <= 4 && comps <= 4ull * (uint64_t)d.num_cu && (max_r <= 2 || comps > 16);
+}
+
 // Two waves per component (N = 512, 1024, r <= 4): for batches that do not
 // fill every compute unit, both waves of a slot share one component's work.
 static bool wide_slots_ok(const mm_ctx &c, const int *ids, size_t count)
@@ -854,12 +860,15 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     // per compute unit, two digit groups per component (6.5 against 7.4 ms for one
     // ciphertext, 12.2 against 12.7 ms for 512 components; 20.3 against 18.2 ms at 1024)
     const uint64_t comps = sum_r(c, ids, count), cu = (uint64_t)d.num_cu;
-    // where the matrix-core kernel applies: the fused shape with one wave per component above
-    // one component per compute unit (630 steps take 7.4 to 7.9 ms for 8 to 1024 components,
-    // 12.8 for 2048, 102 for 16,384), up to that the two digit groups (6.4 ms for 4
-    // components, 7.5 for 148, 12.2 for 512)
-    if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};
     const bool two_wave = wide_slots_ok(c, ids, count);
+    // where the matrix-core kernel applies (630 steps, ms): two waves per component up to four
+    // components per compute unit where every ciphertext fits such slots (148 components 7.0,
+    // 400 7.9, 1024 9.2; two digit groups 7.5, 11.0, 19.1; one wave 8.0, 8.8, 9.6; with
+    // r <= 2 from the first ciphertext on, 4.2 against 6.1 for one of r = 1; with r = 4
+    // one takes 6.3 either way and up to 16 components keep the digit groups), else one
+    // wave per component above one per compute unit (13.2 for 1600 against 16.2 with two)
+    if (mx_two_waves(c, d, comps, two_wave ? max_r(c, ids, count) : 8u)) return Sched{8, ks_default(c, d, count), 2};
+    if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
         (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
         return Sched{0, ks_default(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};

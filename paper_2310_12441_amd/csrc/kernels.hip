@@ -758,8 +758,8 @@ static void launch_br_n(const BrArgs &A, int gw, int grid, hipStream_t st, int w
 
 void launch_blind_rotate(uint32_t N, const BrArgs &A, int gw, int grid, hipStream_t st, int wpp, int ntt)
 {
-    if (A.mx.cst && N == 1024 && gw == 8 && (wpp == 0 || wpp == 1) && ntt == 0) {
-        launch_mx_rotate(A, grid, st);
+    if (A.mx.cst && N == 1024 && gw == 8 && wpp <= 2 && ntt == 0) {
+        launch_mx_rotate(A, grid, st, wpp);
         return;
     }
     switch (N) {

@@ -172,7 +172,8 @@ void launch_wide_init(uint32_t N, int npr, const WideArgs &A, uint32_t num_tasks
 void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st,
                       int wpp = 0, int dg = 1, bool ps = false);
 // The blind rotation and one CMux step on the matrix cores.
-void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st);
+// (the rotation: wpp waves per component, 1 or 2)
+void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st, int wpp);
 void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
 bool mx_supports(uint32_t N, int npr);
 // polys polynomials of one prime's NTT-domain key (bit-reversed, x 2^32 / N) into the order and

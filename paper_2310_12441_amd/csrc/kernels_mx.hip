@@ -149,9 +149,11 @@ __device__ __forceinline__ void mx_mac(int t, const int32_t (&lo)[16], const int
     }
 }
 
-// Digit u of the fields y of both parts as signed bytes, the first stage's operand, into
-// the wave's LDS (each lane reads back only its own).
-__device__ __forceinline__ void mx_digits(const uint32_t (&y)[2][16], uint32_t l, uint32_t log2B, const MxArgs &X,
+// Digit u of the fields y of P parts as signed bytes ([u][part]), the first stage's operand,
+// into the wave's LDS (each lane reads back only its own); with one part a zero polynomial
+// behind an odd number of digits.
+template <int P>
+__device__ __forceinline__ void mx_digits(const uint32_t (&y)[P][16], uint32_t l, uint32_t log2B, const MxArgs &X,
                                           int lane, v4i *dig)
 {
 #pragma unroll
@@ -159,7 +161,7 @@ __device__ __forceinline__ void mx_digits(const uint32_t (&y)[2][16], uint32_t l
         if (u >= l) break;
         const uint32_t sh = u * log2B, wd = log2B + (u + 1 == l ? 1u : 0u);
 #pragma unroll
-        for (int part = 0; part < 2; part++) {
+        for (int part = 0; part < P; part++) {
             v4i d;
 #pragma unroll
             for (int q = 0; q < 4; q++) {
@@ -168,54 +170,81 @@ __device__ __forceinline__ void mx_digits(const uint32_t (&y)[2][16], uint32_t l
                 for (int s = 0; s < 4; s++) p |= __builtin_amdgcn_ubfe(y[part][4 * q + s], sh, wd) << (8 * s);
                 d[q] = (int32_t)((p + X.bias) ^ BAL);
             }
-            dig[(2 * u + part) * 64 + lane] = d;
+            dig[(P * u + part) * 64 + lane] = d;
         }
     }
+    if (P == 1 && (l & 1)) dig[l * 64 + lane] = v4i{};
 }
 
-// acc += the digit polynomials times their key rows: digits of a (part 0) meet rows l + u,
-// digits of b rows u (eq. def:gsw).
+// acc += two digit polynomials (operands x) times their key rows kr.
+__device__ __forceinline__ void mx_pair(const v4i (&x)[2], const v4i *const (&kr)[2], const v4i *cst, int lane,
+                                        const MxArgs &X, const ModS &m, int64_t (&acc)[2][16])
+{
+    int32_t lo[2][16], hi[2][16];
+    v4i z[2][4], k[2][2][4];
+    int64_t s4[4];
+    int32_t r4[4];
+    auto request = [&](int p) {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int o = 0; o < 2; o++) k[p][o][q] = kr[p][(4 * o + q) * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        v16i c[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) c[j] = mfma(x[p], cst[(MX_FA + j) * 64 + lane], v16i{});
+        if (p == 1) {
+#pragma unroll
+            for (int t = 0; t < 8; t++) mx_twist(t, lo[0], hi[0], cst + MX_TWF * 64 + lane, 64, X, m, s4, z[0]);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            lo[p][v] = c[0][v] + (int32_t)((uint32_t)c[1][v] << 8);
+            hi[p][v] = c[2][v] + (int32_t)((uint32_t)c[3][v] << 8);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    request(0);
+    mx_stage<true>(cst + MX_FB * 64, z[0], lane, lo[0], hi[0],
+                   [&](int t) { mx_twist(t, lo[1], hi[1], cst + MX_TWF * 64 + lane, 64, X, m, s4, z[1]); });
+    request(1);
+    mx_stage<true>(cst + MX_FB * 64, z[1], lane, lo[1], hi[1], [&](int t) { mx_mac(t, lo[0], hi[0], k[0], X, m, r4, acc); });
+#pragma unroll
+    for (int t = 0; t < 8; t++) mx_mac(t, lo[1], hi[1], k[1], X, m, r4, acc);
+}
+
+// Row of the key block K as operand words.
+__device__ __forceinline__ const v4i *mx_row(const int32_t *K, uint32_t row)
+{
+    return reinterpret_cast<const v4i *>(K + (size_t)row * 2 * MXN);
+}
+
+// acc += the digit polynomials of both parts ([u][part]) times their key rows: digits of a
+// (part 0) meet rows l + u, digits of b rows u (eq. def:gsw).
 __device__ __forceinline__ void mx_products(const v4i *dig, const v4i *cst, const int32_t *K, uint32_t l, int lane,
                                             const MxArgs &X, const ModS &m, int64_t (&acc)[2][16])
 {
     for (uint32_t u = 0; u < l; u++) {
         __asm__ volatile("" ::: "memory");  // constants and key words are read where they are used
-        int32_t lo[2][16], hi[2][16];
-        v4i z[2][4], k[2][2][4];
-        int64_t s4[4];
-        int32_t r4[4];
-        auto request = [&](int p) {
-            const v4i *kr = reinterpret_cast<const v4i *>(K + (size_t)(p ? u : l + u) * 2 * MXN) + lane;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-#pragma unroll
-                for (int o = 0; o < 2; o++) k[p][o][q] = kr[(4 * o + q) * 64];
-            __builtin_amdgcn_sched_barrier(0);
-        };
         const v4i x[2] = {dig[2 * u * 64 + lane], dig[(2 * u + 1) * 64 + lane]};
-#pragma unroll
-        for (int p = 0; p < 2; p++) {
-            v16i c[4];
-#pragma unroll
-            for (int j = 0; j < 4; j++) c[j] = mfma(x[p], cst[(MX_FA + j) * 64 + lane], v16i{});
-            if (p == 1) {
-#pragma unroll
-                for (int t = 0; t < 8; t++) mx_twist(t, lo[0], hi[0], cst + MX_TWF * 64 + lane, 64, X, m, s4, z[0]);
-            }
-#pragma unroll
-            for (int v = 0; v < 16; v++) {
-                lo[p][v] = c[0][v] + (int32_t)((uint32_t)c[1][v] << 8);
-                hi[p][v] = c[2][v] + (int32_t)((uint32_t)c[3][v] << 8);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        request(0);
-        mx_stage<true>(cst + MX_FB * 64, z[0], lane, lo[0], hi[0],
-                       [&](int t) { mx_twist(t, lo[1], hi[1], cst + MX_TWF * 64 + lane, 64, X, m, s4, z[1]); });
-        request(1);
-        mx_stage<true>(cst + MX_FB * 64, z[1], lane, lo[1], hi[1], [&](int t) { mx_mac(t, lo[0], hi[0], k[0], X, m, r4, acc); });
-#pragma unroll
-        for (int t = 0; t < 8; t++) mx_mac(t, lo[1], hi[1], k[1], X, m, r4, acc);
+        const v4i *const kr[2] = {mx_row(K, l + u), mx_row(K, u)};
+        mx_pair(x, kr, cst, lane, X, m, acc);
+    }
+}
+
+// The same for one part's digits ([u], a zero polynomial behind an odd number), by pairs of u.
+__device__ __forceinline__ void mx_products_part(const v4i *dig, int part, const v4i *cst, const int32_t *K, uint32_t l,
+                                                 int lane, const MxArgs &X, const ModS &m, int64_t (&acc)[2][16])
+{
+    const uint32_t first = part ? 0 : l;
+    for (uint32_t u = 0; u < l; u += 2) {
+        __asm__ volatile("" ::: "memory");
+        const v4i x[2] = {dig[u * 64 + lane], dig[(u + 1) * 64 + lane]};
+        const v4i *const kr[2] = {mx_row(K, first + u), mx_row(K, first + min(u + 1, l - 1))};
+        mx_pair(x, kr, cst, lane, X, m, acc);
     }
 }
 
@@ -270,6 +299,36 @@ __device__ __forceinline__ void mx_inverse(const int64_t (&acc)[2][16], const v4
     for (int q = 0; q < 4; q++) last(1, q);
 }
 
+// The same for one part alone: out(v, x).
+template <class Out>
+__device__ __forceinline__ void mx_inverse_part(const int64_t (&acc)[16], const v4i *cst, int lane, const MxArgs &X,
+                                                const ModS &m, Out out)
+{
+    __asm__ volatile("" ::: "memory");
+    const int neg = ((32 - lane) & 31) | (lane & 32);
+    int32_t lo[16], hi[16], o[4];
+    v4i z[4], tw[8];
+    int64_t s4[4];
+#pragma unroll
+    for (int j = 0; j < 8; j++) tw[j] = reinterpret_cast<const v4i *>(X.cst)[MX_VECS + j * 64 + lane];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; q++) mx_cut(q, acc, X, m, s4, z);
+    mx_stage<false>(cst + MX_FB * 64, z, neg, lo, hi, [](int) {});
+#pragma unroll
+    for (int t = 0; t < 8; t++) mx_twist(t, lo, hi, tw, 1, X, m, s4, z);
+    mx_stage<true>(cst + MX_FB * 64, z, neg, lo, hi, [](int) {});
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const v4i f = cst[MX_FIN * 64 + 4 * q + 2 * (lane >> 5)], f16 = cst[MX_FIN * 64 + 4 * q + 2 * (lane >> 5) + 1];
+#pragma unroll
+        for (int s = 0; s < 4; s++) s4[s] = (int64_t)lo[4 * q + s] * f[s] + (int64_t)hi[4 * q + s] * f16[s];
+        redc4(s4, m, o);
+#pragma unroll
+        for (int s = 0; s < 4; s++) out(4 * q + s, min((uint32_t)o[s], (uint32_t)o[s] + (uint32_t)m.Q));
+    }
+}
+
 // Sums of one key's products, folded so that another key's fit on top below 2^63.
 __device__ __forceinline__ void mx_fold(int64_t (&acc)[2][16], const MxArgs &X)
 {
@@ -295,7 +354,7 @@ __device__ __forceinline__ uint32_t mx_field(uint32_t src, uint32_t own, uint32_
 
 // ------------------------------------------------------------------ the fused blind rotation
 
-// All n CMux steps of up to eight ring components per workgroup, one wave per component
+// All n CMux steps of up to eight ring components per workgroup, W = 1 wave per component
 // (the groups and tasks of k_blind_rotate): the accumulators stay in LDS, one buffer,
 // two workgroup barriers per step (every rotation has read; every component is written).
 //
@@ -307,16 +366,23 @@ __device__ __forceinline__ uint32_t mx_field(uint32_t src, uint32_t own, uint32_
 // digits (64 KB) and the accumulators (64 KB) of eight waves.  Measured for 16,384 components,
 // 630 steps: 102 ms, against 183 for k_wide_step<1024, 1, 1, 4> and 204 for k_blind_rotate;
 // one workgroup alone 7.4 ms with one wave per SIMD, 12.8 with two.
-template <int KEYS>
+//
+// W = 2: two waves per component, up to four components: wave p takes part p of the rotation,
+// its digits' products onto both parts' sums, and part p of the inverse; the sums of the
+// other part go to its wave through LDS before the second barrier.
+template <int KEYS, int W>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_rotate(BrArgs A)
 {
+    constexpr int P = 2 / W;  // parts per wave
     __shared__ v4i cst[MX_VECS];
-    __shared__ v4i digits[8][MX_MAX_L * 2 * 64];
-    __shared__ uint32_t accs[8][2 * MXN];
+    __shared__ v4i digits[8][MX_MAX_L * P * 64];
+    __shared__ uint32_t accs[8 / W][2 * MXN];
+    __shared__ v4i sums[W == 2 ? 8 : 1][8 * 64];
     for (int t = threadIdx.x; t < MX_VECS; t += 512) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int base = (lane & 31) + 128 * (lane >> 5);  // + mx_off(v): the coefficient of register v
-    uint32_t *const own = accs[wave] + base;
+    const int slot = wave / W, p0 = W == 2 ? wave & 1 : 0;
+    uint32_t *const own = accs[slot] + p0 * MXN + base;
     v4i *const dig = digits[wave];
     const uint32_t Q = A.Q;
     const ModS m{(int32_t)Q, A.qn};
@@ -328,7 +394,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // an opaque copy of the lane's position: the addresses of a group's ends stay out of the steps
         int pos = base;
         __asm__("" : "+v"(pos));
-        uint32_t *const mine = accs[wave] + pos;
+        uint32_t *const mine = accs[slot] + p0 * MXN + pos;
         // Phi(b') (0, V) or the stored state; each lane writes the words it alone reads back
         // as its own, and the step's first barrier makes them visible to the rotations
         if (has && (T.flags & TASK_INIT)) {
@@ -336,19 +402,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             phi_row(__builtin_amdgcn_readfirstlane(modswitch_dev(ct[A.n], T.q_in, M)), r, T.comp, src, e);
             const uint32_t *V = A.tv + T.tv_off + (size_t)src * MXN;
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const uint32_t i2 = (pos + mx_off(v) + 2 * MXN - (e % (2 * MXN))) % (2 * MXN);
-                const uint32_t x = V[i2 & (MXN - 1)];
-                mine[mx_off(v)] = 0;
-                mine[MXN + mx_off(v)] = (i2 >= (uint32_t)MXN) ? (x ? Q - x : 0) : x;
-            }
-        } else if (has) {
-            const uint32_t *S = A.acc_state + T.acc_off + (size_t)T.comp * 2 * MXN + pos;
+            for (int p = 0; p < P; p++)
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                mine[mx_off(v)] = S[mx_off(v)];
-                mine[MXN + mx_off(v)] = S[MXN + mx_off(v)];
-            }
+                for (int v = 0; v < 16; v++) {
+                    uint32_t x = 0;
+                    if (p0 + p == 1) {
+                        const uint32_t i2 = (pos + mx_off(v) + 2 * MXN - (e % (2 * MXN))) % (2 * MXN);
+                        x = V[i2 & (MXN - 1)];
+                        if (i2 >= (uint32_t)MXN) x = x ? Q - x : 0;
+                    }
+                    mine[p * MXN + mx_off(v)] = x;
+                }
+        } else if (has) {
+            const uint32_t *S = A.acc_state + T.acc_off + (size_t)T.comp * 2 * MXN + p0 * MXN + pos;
+#pragma unroll
+            for (int p = 0; p < P; p++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) mine[p * MXN + mx_off(v)] = S[p * MXN + mx_off(v)];
         }
         const uint32_t lim = T.steps ? min(T.steps, (uint32_t)A.steps) : (uint32_t)A.steps;
         for (int s = 0; s < A.steps; s++) {
@@ -364,49 +434,76 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 for (int key = 0; key < KEYS; key++) {
                     uint32_t src, e;
                     phi_row(key == 0 ? (M - am) % M : am, r, T.comp, src, e);
-                    const uint32_t *sp = accs[wave - T.comp + src];
+                    const uint32_t *sp = accs[slot - T.comp + src] + p0 * MXN;
                     const uint32_t rb = (uint32_t)base + 2 * MXN - (e % (2 * MXN));
-                    uint32_t y[2][16];
+                    uint32_t y[P][16];
 #pragma unroll
                     for (int v = 0; v < 16; v++) {
                         const uint32_t i2 = rb + mx_off(v);
                         const uint32_t at = i2 & (MXN - 1);
                         const uint32_t flip = 0u - ((i2 >> 10) & 1u);
                         const uint32_t fq = flip & (Q + 1);
-                        y[0][v] = mx_field(sp[at], own[mx_off(v)], flip, fq, Q, A.mx, A.sg);
-                        y[1][v] = mx_field(sp[MXN + at], own[MXN + mx_off(v)], flip, fq, Q, A.mx, A.sg);
+#pragma unroll
+                        for (int p = 0; p < P; p++)
+                            y[p][v] = mx_field(sp[p * MXN + at], own[p * MXN + mx_off(v)], flip, fq, Q, A.mx, A.sg);
                     }
-                    mx_digits(y, A.l, A.log2B, A.mx, lane, dig);
-                    mx_products(dig, cst, A.mx.bsk + ((size_t)i * KEYS + key) * (4u * A.l * MXN), A.l, lane, A.mx, m,
-                                acc);
+                    mx_digits<P>(y, A.l, A.log2B, A.mx, lane, dig);
+                    const int32_t *K = A.mx.bsk + ((size_t)i * KEYS + key) * (4u * A.l * MXN);
+                    if constexpr (W == 1) mx_products(dig, cst, K, A.l, lane, A.mx, m, acc);
+                    else mx_products_part(dig, p0, cst, K, A.l, lane, A.mx, m, acc);
                     if (KEYS == 2 && key == 0) mx_fold(acc, A.mx);
+                }
+                if constexpr (W == 2) {
+                    // the other part's sums to its wave
+#pragma unroll
+                    for (int v = 0; v < 8; v++) {
+                        const int64_t t0 = p0 ? acc[0][2 * v] : acc[1][2 * v];
+                        const int64_t t1 = p0 ? acc[0][2 * v + 1] : acc[1][2 * v + 1];
+                        sums[wave][v * 64 + lane] = v4i{(int32_t)t0, (int32_t)(t0 >> 32), (int32_t)t1, (int32_t)(t1 >> 32)};
+                    }
                 }
             }
             __syncthreads();  // every rotation of the step has read the accumulators
-            if (active)
-                mx_inverse(acc, cst, lane, A.mx, m, [&](int p, int v, uint32_t x) {
+            if (active) {
+                auto store = [&](int p, int v, uint32_t x) {
                     uint32_t *o = own + p * MXN + mx_off(v);
                     *o = add_q(*o, x, Q);
-                });
+                };
+                if constexpr (W == 1) {
+                    mx_inverse(acc, cst, lane, A.mx, m, store);
+                } else {
+                    int64_t mysum[16];
+#pragma unroll
+                    for (int v = 0; v < 8; v++) {
+                        const v4i t = sums[wave ^ 1][v * 64 + lane];
+                        const int64_t t0 = (int64_t)((uint64_t)(uint32_t)t[1] << 32 | (uint32_t)t[0]);
+                        const int64_t t1 = (int64_t)((uint64_t)(uint32_t)t[3] << 32 | (uint32_t)t[2]);
+                        mysum[2 * v] = (p0 ? acc[1][2 * v] : acc[0][2 * v]) + t0;
+                        mysum[2 * v + 1] = (p0 ? acc[1][2 * v + 1] : acc[0][2 * v + 1]) + t1;
+                    }
+                    mx_inverse_part(mysum, cst, lane, A.mx, m, [&](int v, uint32_t x) { store(0, v, x); });
+                }
+            }
         }
         if (has) {
             if (T.flags & TASK_STORE) {
-                uint32_t *S = A.acc_state + T.acc_off + (size_t)T.comp * 2 * MXN + pos;
+                uint32_t *S = A.acc_state + T.acc_off + (size_t)T.comp * 2 * MXN + p0 * MXN + pos;
 #pragma unroll
-                for (int v = 0; v < 16; v++) {
-                    S[mx_off(v)] = mine[mx_off(v)];
-                    S[MXN + mx_off(v)] = mine[MXN + mx_off(v)];
-                }
+                for (int p = 0; p < P; p++)
+#pragma unroll
+                    for (int v = 0; v < 16; v++) S[p * MXN + mx_off(v)] = mine[p * MXN + mx_off(v)];
             }
             if ((T.flags & TASK_EXTRACT) && T.comp == 0 && T.i0 + lim >= A.n) {
                 // (A_0, -A_{N-1}, ..., -A_1; B_0) (eq. equ-sam-extr)
                 uint32_t *o = A.ext_out + (size_t)T.ct * (MXN + 1);
+                if (p0 == 0) {
 #pragma unroll
-                for (int v = 0; v < 16; v++) {
-                    const uint32_t idx = pos + mx_off(v), x = mine[mx_off(v)];
-                    o[(MXN - idx) & (MXN - 1)] = idx ? (x ? Q - x : 0) : x;
+                    for (int v = 0; v < 16; v++) {
+                        const uint32_t idx = pos + mx_off(v), x = mine[mx_off(v)];
+                        o[(MXN - idx) & (MXN - 1)] = idx ? (x ? Q - x : 0) : x;
+                    }
                 }
-                if (lane == 0) o[MXN] = mine[MXN];
+                if (p0 + P == 2 && lane == 0) o[MXN] = mine[(1 - p0) * MXN];
             }
         }
         __syncthreads();  // the next group's accumulators take this one's place
@@ -466,7 +563,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 y[0][v] = mx_field(sp[at], own[mx_off(v)], flip, fq, Q, A.mx, A.sg);
                 y[1][v] = mx_field(sp[MXN + at], own[MXN + mx_off(v)], flip, fq, Q, A.mx, A.sg);
             }
-            mx_digits(y, A.l, A.log2B, A.mx, lane, dig);
+            mx_digits<2>(y, A.l, A.log2B, A.mx, lane, dig);
             mx_products(dig, cst, A.mx.bsk + ((size_t)i * KEYS + key) * (4u * A.l * MXN), A.l, lane, A.mx, m, acc);
             if (KEYS == 2 && key == 0) mx_fold(acc, A.mx);
         }
@@ -835,10 +932,17 @@ void launch_mx_keys(uint32_t N, const uint32_t *src, uint32_t *dst, size_t polys
     hipLaunchKernelGGL(k_mx_keys, dim3((uint32_t)polys), dim3(256), 0, st, src, dst, logN, Q, qn, two64, block, primes, pr);
 }
 
-void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st)
+void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st, int wpp)
 {
-    if (A.keys == 2) hipLaunchKernelGGL(k_mx_rotate<2>, dim3(grid), dim3(512), 0, st, A);
-    else hipLaunchKernelGGL(k_mx_rotate<1>, dim3(grid), dim3(512), 0, st, A);
+#define R_(w)                                                                                \
+    if (A.keys == 2) hipLaunchKernelGGL((k_mx_rotate<2, w>), dim3(grid), dim3(512), 0, st, A); \
+    else hipLaunchKernelGGL((k_mx_rotate<1, w>), dim3(grid), dim3(512), 0, st, A)
+    if (wpp == 2) {
+        R_(2);
+    } else {
+        R_(1);
+    }
+#undef R_
 }
 
 void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st)

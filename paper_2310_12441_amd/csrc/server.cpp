@@ -438,14 +438,17 @@ void Server::launch(Part &p)
     bool glob = global;
     if (switchable) {
         // the rule of the batched path's default schedule: at most two components per
-        // compute unit, or four where the components cannot take two-wave slots
+        // compute unit, or four where the components cannot take two-wave slots; on the
+        // matrix cores what its two-wave slots do not take, up to one per compute unit
         uint64_t comps = 0;
-        bool wide8 = false;
+        uint32_t max_r = 1;
         for (auto &a : p.active) {
             comps += c->tables[a.table].r;
-            wide8 |= c->tables[a.table].r > 4;
+            max_r = std::max(max_r, c->tables[a.table].r);
         }
-        glob = comps <= 2ull * (uint64_t)d.num_cu || (wide8 && comps <= 4ull * (uint64_t)d.num_cu);
+        const uint64_t cu = (uint64_t)d.num_cu;
+        if (d.mx_cst) glob = !mx_two_waves(*c, d, comps, max_r) && comps <= cu;
+        else glob = comps <= 2 * cu || (max_r > 4 && comps <= 4 * cu);
     }
     if (glob) {
         launch_global(p, fresh);

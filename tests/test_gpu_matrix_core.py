@@ -29,11 +29,11 @@ def _context(p, seed, draws=None):
     return ctx, oracle.KeySet(p, draws)
 
 
-def _fused(ctx, ids):
-    """Pin the fused shape with one wave per component, lockstep schedule."""
+def _fused(ctx, ids, waves=1):
+    """Pin the fused shape with `waves` waves per component, lockstep schedule."""
     for k in range(ctx.schedule_count(ids)):
         d = ctx.schedule_describe(ids, k)
-        if d[0] == 8 and d[3] == 1 and d[5] == 0:
+        if d[0] == 8 and d[3] == waves and d[5] == 0:
             return ctx.set_schedule(ids, k)
     raise AssertionError("no fused schedule")
 
@@ -69,6 +69,10 @@ def test_fused_steps_and_bootstrap(l, log2_B, ternary, Q):
     out = ctx.bootstrap(ids, np.array(cts), q_out=p.Q)
     for j, (r, q) in enumerate(rs):
         np.testing.assert_array_equal(out[j], oracle.bootstrap(p, r, keys.bsk, keys.ksk, Vs[j], q, p.Q, cts[j]))
+    # two waves per component: r <= 4, with idle slots, and more groups than compute units
+    narrow = [j for j, (r, _) in enumerate(rs) if r <= 4] * 200
+    _fused(ctx, [ids[j] for j in narrow], 2)
+    np.testing.assert_array_equal(ctx.bootstrap([ids[j] for j in narrow], np.array(cts)[narrow], q_out=p.Q), out[narrow])
     ctx.close()
 
 
