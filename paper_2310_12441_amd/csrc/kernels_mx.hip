@@ -512,32 +512,35 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // ------------------------------------------------------------------ one CMux step
 
+// One wave per component; workgroups of eight waves, or of four while that gives every component
+// a SIMD of its own (launch_mx_step).
 template <int KEYS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_step(WideArgs A, uint32_t num_tasks)
 {
     __shared__ v4i cst[MX_VECS];
     __shared__ v4i digits[8][MX_MAX_L * 2 * 64];
-    for (int t = threadIdx.x; t < MX_VECS; t += 512) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
+    for (int t = threadIdx.x; t < MX_VECS; t += blockDim.x) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int base = (lane & 31) + 128 * (lane >> 5);
+    const uint32_t waves = blockDim.x >> 6;
     v4i *const dig = digits[wave];
     const uint32_t Q = A.Q[0];
     const ModS m{(int32_t)Q, A.qn[0]};
-    const uint32_t slot = xcd_item(blockIdx.x, gridDim.x) * 8 + wave;
-    for (uint32_t item = slot; item < num_tasks; item += gridDim.x * 8) {
+    const uint32_t slot = xcd_item(blockIdx.x, gridDim.x) * waves + wave;
+    for (uint32_t item = slot; item < num_tasks; item += gridDim.x * waves) {
         const WideTask &T = A.tasks[item];
         const uint32_t i = __builtin_amdgcn_readfirstlane(T.i0) + A.step;
         const uint32_t r = __builtin_amdgcn_readfirstlane(T.r), comp = __builtin_amdgcn_readfirstlane(T.comp);
         const uint32_t q_in = __builtin_amdgcn_readfirstlane(T.q_in);
-        const uint64_t off = T.acc_off;
-        const uint32_t *own = A.acc_rd + off + (size_t)comp * 2 * MXN + base;
-        uint32_t *wr = A.acc_wr + off + (size_t)comp * 2 * MXN + base;
+        const uint32_t *const ct_acc = A.acc_rd + T.acc_off, *const own = ct_acc + (size_t)comp * 2 * MXN;
+        uint32_t *const wr = A.acc_wr + T.acc_off + (size_t)comp * 2 * MXN;
+        uint32_t base = (lane & 31) + 128 * (lane >> 5);
+        __asm__("" : "+v"(base));  // opaque: addresses are formed where they are used
         if (i >= A.n) {
 #pragma unroll
             for (int v = 0; v < 16; v++) {
-                wr[mx_off(v)] = own[mx_off(v)];
-                wr[MXN + mx_off(v)] = own[MXN + mx_off(v)];
+                wr[base + mx_off(v)] = own[base + mx_off(v)];
+                wr[base + MXN + mx_off(v)] = own[base + MXN + mx_off(v)];
             }
             continue;
         }
@@ -551,31 +554,40 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int key = 0; key < KEYS; key++) {
             uint32_t src, e;
             phi_row(key == 0 ? (M - am) % M : am, r, comp, src, e);
-            const uint32_t *sp = A.acc_rd + off + (size_t)src * 2 * MXN;
-            const uint32_t rb = (uint32_t)base + 2 * MXN - (e % (2 * MXN));
+            const uint32_t *sp = ct_acc + (size_t)src * 2 * MXN;
+            const uint32_t rb = base + 2 * MXN - (e % (2 * MXN));
+            // every word is requested before the first is used
+            uint32_t vo[2][16], vs[2][16];
+#pragma unroll
+            for (int p = 0; p < 2; p++)
+#pragma unroll
+                for (int v = 0; v < 16; v++) {
+                    vo[p][v] = own[base + p * MXN + mx_off(v)];
+                    vs[p][v] = sp[p * MXN + ((rb + mx_off(v)) & (MXN - 1))];
+                }
+            __builtin_amdgcn_sched_barrier(0);
             uint32_t y[2][16];
 #pragma unroll
             for (int v = 0; v < 16; v++) {
-                const uint32_t i2 = rb + mx_off(v);
-                const uint32_t at = i2 & (MXN - 1);
-                const uint32_t flip = 0u - ((i2 >> 10) & 1u);
+                const uint32_t flip = 0u - (((rb + mx_off(v)) >> 10) & 1u);
                 const uint32_t fq = flip & (Q + 1);
-                y[0][v] = mx_field(sp[at], own[mx_off(v)], flip, fq, Q, A.mx, A.sg);
-                y[1][v] = mx_field(sp[MXN + at], own[MXN + mx_off(v)], flip, fq, Q, A.mx, A.sg);
+#pragma unroll
+                for (int p = 0; p < 2; p++) y[p][v] = mx_field(vs[p][v], vo[p][v], flip, fq, Q, A.mx, A.sg);
             }
             mx_digits<2>(y, A.l, A.log2B, A.mx, lane, dig);
             mx_products(dig, cst, A.mx.bsk + ((size_t)i * KEYS + key) * (4u * A.l * MXN), A.l, lane, A.mx, m, acc);
             if (KEYS == 2 && key == 0) mx_fold(acc, A.mx);
         }
         uint32_t old[2][16];  // this component's accumulator again, requested early
-        __builtin_amdgcn_sched_barrier(0);
+        uint32_t pos = base;
+        __asm__("" : "+v"(pos));
 #pragma unroll
         for (int p = 0; p < 2; p++)
 #pragma unroll
-            for (int v = 0; v < 16; v++) old[p][v] = own[p * MXN + mx_off(v)];
+            for (int v = 0; v < 16; v++) old[p][v] = own[pos + p * MXN + mx_off(v)];
         __builtin_amdgcn_sched_barrier(0);
         mx_inverse(acc, cst, lane, A.mx, m,
-                   [&](int p, int v, uint32_t x) { wr[p * MXN + mx_off(v)] = add_q(old[p][v], x, Q); });
+                   [&](int p, int v, uint32_t x) { wr[pos + p * MXN + mx_off(v)] = add_q(old[p][v], x, Q); });
     }
 }
 
@@ -954,9 +966,10 @@ void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint3
         return;
     }
     if (npr != 1 || N != 1024) return;
-    const uint32_t grid = std::min<uint32_t>((num_tasks + 7) / 8, A.mx.num_cu);
-    if (keys == 2) hipLaunchKernelGGL(k_mx_step<2>, dim3(grid), dim3(512), 0, st, A, num_tasks);
-    else hipLaunchKernelGGL(k_mx_step<1>, dim3(grid), dim3(512), 0, st, A, num_tasks);
+    const uint32_t waves = num_tasks <= 4 * A.mx.num_cu ? 4 : 8;
+    const uint32_t grid = std::min<uint32_t>((num_tasks + waves - 1) / waves, A.mx.num_cu);
+    if (keys == 2) hipLaunchKernelGGL(k_mx_step<2>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
+    else hipLaunchKernelGGL(k_mx_step<1>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
 }
 
 bool mx_supports(uint32_t N, int npr) { return N == (npr == 2 ? 2048u : 1024u); }

@@ -621,8 +621,15 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
                       int wpp, int dg, bool ps)
 {
     if (A.mx.cst && dg == 1 && !ps) {
-        launch_mx_step(N, npr, keys, A, num_tasks, st);
-        return;
+        // the matrix cores; at one prime and up to 3/2 components per compute unit the two digit
+        // groups below stay the faster shape (630 steps, ms: 16 components 6.3 against 10.2,
+        // 256 7.8 against 10.8; 512 12.2 against 11.3)
+        if (npr == 2 || 2 * num_tasks > 3 * A.mx.num_cu) {
+            launch_mx_step(N, npr, keys, A, num_tasks, st);
+            return;
+        }
+        dg = 2;
+        wpp = 4;
     }
     if (ps && npr == 2) {
         if (dg == 2 && N == 1024) ps_launch<1024, 2, 2>(keys, A, num_tasks, st);
