@@ -872,7 +872,16 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
         (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
         return Sched{0, ks_default(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};
-    return Sched{8, ks_default(c, d, count), comps <= 4 * cu && two_wave ? 2 : 0};
+    if (comps <= 4 * cu && two_wave) return Sched{8, ks_default(c, d, count), 2};
+    // rings of several waves per component: groups of four waves (two workgroups per compute
+    // unit, each its own barriers) where the last round of eight-wave groups would be at most
+    // half full -- N = 4096, r = 1, ms: 2 ciphertexts 23.4 against 34.2, 256 28.9 against 39.5, 700
+    // 46.7 against 66.9; 512 34.6 either way, 1000 67.7 against 67.3
+    const uint64_t wpp = (uint64_t)dev::waves_per_poly(c.p.N), round = 8 / std::min<uint64_t>(wpp, 8) * cu;
+    const uint64_t rest = comps % round;
+    if (wpp > 1 && max_r(c, ids, count) * wpp <= 4 && rest > 0 && 2 * rest <= round)
+        return Sched{4, ks_default(c, d, count), 0};
+    return Sched{8, ks_default(c, d, count), 0};
 }
 
 static int br_grid(const Device &d, int groups, int gw) { return std::min(groups, d.num_cu * (gw == 4 ? 2 : 1)); }
