@@ -621,23 +621,19 @@ uint32_t ks_splits(const mm_ctx &c, const Device &d, size_t count)
 static uint32_t ks_lanes_splits(const mm_ctx &c, const Device &d, size_t count)
 {
     const size_t blocks = ((c.p.n + 1 + 63) / 64) * ((count + 255) / 256);
-    return (uint32_t)std::max<size_t>(1, std::min<size_t>(8, 2 * (size_t)d.num_cu / blocks));
+    return (uint32_t)std::max<size_t>(1, std::min<size_t>(c.p.N / 8, 2 * (size_t)d.num_cu / blocks));
 }
 
-// Key-switch schedule for `count` samples: one ciphertext per lane for large
-// batches, the LDS-tiled kernel with columns in lanes (cpw > 0) for medium
-// ones, the i-split kernel for small ones.
+// Key-switch schedule for `count` samples: one ciphertext per lane wherever a coordinate's
+// rows fit its LDS tile (n = 630, N = 1024, us, against the kernel that was best before: 1
+// sample 78 against 84, 33 82 against 654, 100 106 against 1433, 255 182 against 2456, 512 262
+// against 502 with at most 8 splits, 1000 484 against 644), else the i-split kernel.
 KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 {
     KsSched k;
-    const uint32_t rows = c.p.l_ks << c.p.log2_Bks;
-    if (count >= 512 && rows <= (uint32_t)dev::KS_TILED_MAX_ROWS) {
+    if ((c.p.l_ks << c.p.log2_Bks) <= (uint32_t)dev::KS_TILED_MAX_ROWS) {
         k.cpw = KS_LANES;
         k.P = ks_lanes_splits(c, d, count);
-    } else if (count >= 256 && rows <= (uint32_t)dev::KS_TILED_MAX_ROWS) {
-        k.cpw = 32;
-        const size_t blocks = ((c.p.n + 1 + 63) / 64) * ((count + 4 * k.cpw - 1) / (4 * k.cpw));
-        k.P = (uint32_t)std::max<size_t>(1, std::min<size_t>(4, (2 * (size_t)d.num_cu + blocks - 1) / blocks));
     } else {
         k.cpw = 0;
         k.P = ks_splits(c, d, count);

@@ -450,25 +450,29 @@ __global__ void __launch_bounds__(256) k_keyswitch_tiled(KsArgs A)
 // work is thus spread over the lanes and amortised over 64 columns; lanes
 // whose digits agree read the same LDS words (broadcasts), and the 66-word row
 // pitch puts the B_ks candidates of one digit on distinct banks.  KSK traffic:
-// one read of the column slice per 256 ciphertexts.  Partial sums over the
-// i-split blockIdx.z go to part (not reduced; every sum < 2^31 l_ks N).
-constexpr int KSL_COLS = KS_TILE_COLS, KSL_PITCH = 66, KSL_CTS = 256, KSL_CHUNK = 32;
+// one read of the column slice per 256 ciphertexts.  With fewer ciphertexts than lanes the
+// waves divide the columns instead: CG = 2 or 4 groups of 32 or 16 columns over 128 or 64
+// ciphertexts.  Partial sums over the i-split blockIdx.z go to part (not reduced; every
+// sum < 2^31 l_ks N).
+constexpr int KSL_COLS = KS_TILE_COLS, KSL_PITCH = 66, KSL_CTS = 256;
 
-template <bool FULL>
+template <bool FULL, int CG>
 __global__ void __launch_bounds__(256, 2) k_keyswitch_lanes(KsArgs A)
 {
+    constexpr int COLS = KSL_COLS / CG, CHUNK = COLS < 32 ? COLS : 32;  // columns per lane, and at a time
     constexpr int ROWS = KS_TILED_MAX_ROWS, V4 = ROWS * KSL_COLS / 4 / 256;
     __shared__ __align__(16) uint32_t tile[2][ROWS * KSL_PITCH];
     const uint32_t W = A.n + 1, Bks = 1u << A.log2Bks, rows = FULL ? (uint32_t)ROWS : A.l_ks * Bks;
     const uint32_t col0 = blockIdx.x * KSL_COLS;
     const uint32_t iper = (A.N + gridDim.z - 1) / gridDim.z;
     const uint32_t i_begin = blockIdx.z * iper, i_end = min(A.N, i_begin + iper);
-    const size_t ct = (size_t)blockIdx.y * KSL_CTS + threadIdx.x;
+    const uint32_t cg = (threadIdx.x >> 6) % CG * COLS;  // first column of the wave's group
+    const size_t ct = (size_t)blockIdx.y * (KSL_CTS / CG) + (threadIdx.x >> 6) / CG * 64 + (threadIdx.x & 63);
     const bool ok = ct < A.count;
     const uint32_t *src = A.lwe_N + (ok ? (A.rows ? (size_t)A.rows[ct] : ct) : 0) * (A.N + 1);
-    uint64_t acc[KSL_COLS];
+    uint64_t acc[COLS];
 #pragma unroll
-    for (int c = 0; c < KSL_COLS; c++) acc[c] = 0;
+    for (int c = 0; c < COLS; c++) acc[c] = 0;
 
     // staging: the tile of coordinate i is rows x 64 contiguous words; thread t
     // moves the 4-word pieces t + 256 k (row (t + 256 k) >> 4, column 4 (t & 15))
@@ -493,14 +497,14 @@ __global__ void __launch_bounds__(256, 2) k_keyswitch_lanes(KsArgs A)
             }
         }
     };
-    // acc += row0 + row1 (64 columns each), or row0 alone, 16 columns at a time
+    // acc += row0 + row1, or row0 alone, at most 32 columns at a time
     // (the compiler is kept from hoisting every LDS read of the rows: registers)
     auto add2 = [&](const uint32_t *r0, const uint32_t *r1) {
 #pragma unroll
-        for (int c0 = 0; c0 < KSL_COLS; c0 += KSL_CHUNK) {
+        for (int c0 = 0; c0 < COLS; c0 += CHUNK) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int c = c0; c < c0 + KSL_CHUNK; c += 2) {
+            for (int c = c0; c < c0 + CHUNK; c += 2) {
                 const uint2 x = *reinterpret_cast<const uint2 *>(r0 + c);
                 const uint2 y = *reinterpret_cast<const uint2 *>(r1 + c);
                 acc[c] += (uint64_t)(x.x + y.x);
@@ -510,10 +514,10 @@ __global__ void __launch_bounds__(256, 2) k_keyswitch_lanes(KsArgs A)
     };
     auto add1 = [&](const uint32_t *r0) {
 #pragma unroll
-        for (int c0 = 0; c0 < KSL_COLS; c0 += KSL_CHUNK) {
+        for (int c0 = 0; c0 < COLS; c0 += CHUNK) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int c = c0; c < c0 + KSL_CHUNK; c += 2) {
+            for (int c = c0; c < c0 + CHUNK; c += 2) {
                 const uint2 x = *reinterpret_cast<const uint2 *>(r0 + c);
                 acc[c] += (uint64_t)x.x;
                 acc[c + 1] += (uint64_t)x.y;
@@ -529,7 +533,7 @@ __global__ void __launch_bounds__(256, 2) k_keyswitch_lanes(KsArgs A)
     for (uint32_t i = i_begin; i < i_end; i++) {
         if (i + 1 < i_end) fetch(i + 1);
         const uint32_t a = src[i];
-        const uint32_t *tb = tile[b];
+        const uint32_t *tb = tile[b] + cg;
         // the row of each digit, two rows at a time (the digit loop stays rolled:
         // unrolled, the compiler keeps too many row reads in flight)
         auto digit = [&](uint32_t j) {
@@ -546,10 +550,10 @@ __global__ void __launch_bounds__(256, 2) k_keyswitch_lanes(KsArgs A)
         b ^= 1;
     }
     if (ok) {
-        uint64_t *o = A.part + ((size_t)blockIdx.z * A.count + ct) * W + col0;
+        uint64_t *o = A.part + ((size_t)blockIdx.z * A.count + ct) * W + col0 + cg;
 #pragma unroll
-        for (int c = 0; c < KSL_COLS; c++)
-            if (col0 + c < W) o[c] = acc[c];
+        for (int c = 0; c < COLS; c++)
+            if (col0 + cg + c < W) o[c] = acc[c];
     }
 }
 
@@ -900,10 +904,20 @@ void launch_keyswitch_tiled(const KsArgs &A, int cpw, uint32_t splits, hipStream
 
 void launch_keyswitch_lanes(const KsArgs &A, uint32_t splits, hipStream_t st)
 {
-    dim3 grid(A.col_tiles, (uint32_t)((A.count + KSL_CTS - 1) / KSL_CTS), splits);
+    const int cg = ks_lanes_groups(A.count);
+    dim3 grid(A.col_tiles, (uint32_t)((A.count + KSL_CTS / cg - 1) / (KSL_CTS / cg)), splits);
     const bool full = (A.l_ks << A.log2Bks) == (uint32_t)KS_TILED_MAX_ROWS;
-    if (full) hipLaunchKernelGGL(k_keyswitch_lanes<true>, grid, dim3(256), 0, st, A);
-    else hipLaunchKernelGGL(k_keyswitch_lanes<false>, grid, dim3(256), 0, st, A);
+#define G_(g)                                                                                     \
+    if (full) hipLaunchKernelGGL((k_keyswitch_lanes<true, g>), grid, dim3(256), 0, st, A);  \
+    else hipLaunchKernelGGL((k_keyswitch_lanes<false, g>), grid, dim3(256), 0, st, A)
+    if (cg == 4) {
+        G_(4);
+    } else if (cg == 2) {
+        G_(2);
+    } else {
+        G_(1);
+    }
+#undef G_
 }
 
 void launch_keyswitch(const KsArgs &A, uint32_t splits, hipStream_t st)

@@ -209,7 +209,9 @@ void launch_sample_extract(const uint32_t *rlwe, uint32_t *lwe, size_t count, ui
                            hipStream_t st);
 void launch_keyswitch(const KsArgs &A, uint32_t splits, hipStream_t st);
 void launch_keyswitch_tiled(const KsArgs &A, int cpw, uint32_t splits, hipStream_t st);
-// one ciphertext per lane, 256 per workgroup, 64 columns (l_ks B_ks <= KS_TILED_MAX_ROWS)
+// one ciphertext per lane, 256 per workgroup, 64 columns (l_ks B_ks <= KS_TILED_MAX_ROWS);
+// fewer ciphertexts: 128 or 64, the columns divided over the waves
+constexpr int ks_lanes_groups(size_t count) { return count <= 64 ? 4 : count <= 128 ? 2 : 1; }
 void launch_keyswitch_lanes(const KsArgs &A, uint32_t splits, hipStream_t st);
 void launch_ks_finalize(const uint64_t *part, const uint32_t *lwe_N, const int32_t *rows, uint32_t *out, size_t count,
                         uint32_t n,
