@@ -727,11 +727,13 @@ int light_global_wpp(const mm_ctx &c)
 // ternary, ms per bootstrap call, both shapes): one ciphertext 19.2 against 38.6,
 // 256 components 30.2 against 41.5, 1024 87.7 against 94.8, 4096 332.1 against
 // 335.3; 8192 669.2 against 663.2 (the shared digit fields computed twice).  Where the
-// matrix-core kernel applies (it takes the other shape's place) up to one: 16 components
-// 17.6 against 26.4, 256 26.6 against 27.0, 384 35.7 against 29.8, 2400 196.6 against 138.7.
+// matrix-core kernels apply (in place of the other shape and of two digit groups) up to 3/2:
+// 16 components 9.5 against 26.3, 256 18.5 against 26.8, 384 27.1 against 29.1, 512 36.0
+// against 32.1.
 bool prime_split(const mm_ctx &c, const Device &d, uint64_t comps)
 {
-    return c.wide && dev::wide_supports_ps(c.p.N, 2) && comps <= (d.mx_cst ? 1ull : 16ull) * (uint64_t)d.num_cu;
+    const uint64_t cu = (uint64_t)d.num_cu;
+    return c.wide && dev::wide_supports_ps(c.p.N, 2) && (d.mx_cst ? 2 * comps <= 3 * cu : comps <= 16 * cu);
 }
 
 // Digit groups of those workgroups: two (N = 1024, 2048) while both primes' workgroups
@@ -739,8 +741,8 @@ bool prime_split(const mm_ctx &c, const Device &d, uint64_t comps)
 // 18.7 against 19.9 ms; 256 components 34.6 against 29.0 ms), else one.
 int prime_split_dg(const mm_ctx &c, const Device &d, uint64_t comps)
 {
-    return prime_split(c, d, comps) && dev::wide_supports_ps(c.p.N, 2, 2) && 2 * comps <= (uint64_t)d.num_cu ? 2
-                                                                                                            : 1;
+    const bool fits = d.mx_cst || 2 * comps <= (uint64_t)d.num_cu;  // (matrix cores: 9.5 against 18.6 ms, any count)
+    return prime_split(c, d, comps) && dev::wide_supports_ps(c.p.N, 2, 2) && fits ? 2 : 1;
 }
 
 // Digit groups per component of light global-path work: two (each group of

@@ -175,6 +175,8 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
 // (the rotation: wpp waves per component, 1 or 2)
 void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st, int wpp);
 void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
+// (two primes, N = 2048: one workgroup per component and prime)
+void launch_mx_split(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
 bool mx_supports(uint32_t N, int npr);
 // polys polynomials of one prime's NTT-domain key (bit-reversed, x 2^32 / N) into the order and
 // scale of MxArgs::bsk; the prime's polynomials are blocks of `block` every primes * block

@@ -668,6 +668,134 @@ __device__ __forceinline__ void mx_wide_pair(const v4i *d0, const v4i *d1, const
     for (int t = 0; t < 8; t++) mx_mac(t, lo[1], hi[1], k[1], X, m, r4, acc);
 }
 
+// Digits of contraction block b of one part: element e of a lane is coefficient 32 i1 + col,
+// i1 = 16 b + 8 half + e.  Every word (own and rotated source, both primes) is requested
+// before the first is used.
+struct MxWords {
+    uint32_t own[2][8], src[2][8];
+};
+
+__device__ __forceinline__ uint32_t mx_wide_at(int b, int lane) { return 32 * (16 * b + 8 * (lane >> 5)) + (lane & 31); }
+
+__device__ __forceinline__ void mx_wide_request(MxWords &d, const uint32_t *own, const uint32_t *src, const WideRow &w,
+                                                int b, int lane)
+{
+    constexpr int N = MxWide::N;
+    const uint32_t at = mx_wide_at(b, lane);
+#pragma unroll
+    for (int p = 0; p < 2; p++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            d.own[p][e] = own[p * N + at + 32 * e];
+            d.src[p][e] = src[p * N + ((at + 32 * e - w.e) & (N - 1))];
+        }
+}
+
+__device__ __forceinline__ void mx_wide_digits(const MxWords &d, const WideRow &w, int b, const WideArgs &A, int lane,
+                                               v4i *dig)
+{
+    constexpr int NB = MxWide::NB;
+    const uint32_t at = mx_wide_at(b, lane);
+    const ModQ m1{A.Q[1], A.qn[1]};
+    const uint64_t hw = (A.Qw - 1) / 2;
+    uint64_t y[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const bool flip = (at + 32 * e < w.e) != w.neg;
+        auto diff = [&](int p) {
+            const uint32_t v = d.src[p][e], Q = A.Q[p];
+            return sub_q(flip && v ? Q - v : v, d.own[p][e], Q);
+        };
+        const uint32_t a0 = diff(0), a1 = diff(1);
+        // x = a0 + Q0 ((a1 - a0) Q0^-1 mod Q1), in [0, Q0 Q1)
+        const uint64_t x = a0 + (uint64_t)A.Q[0] * mont_mul(a1 + A.crt_cq - a0, A.crt_inv, m1);
+        int64_t xc = x > hw ? (int64_t)(x - A.Qw) : (int64_t)x;
+        if (A.sg) xc = (xc + (1ll << (A.sg - 1))) >> A.sg;
+        y[e] = (uint64_t)xc + A.goff;
+    }
+    for (uint32_t u = 0; u < A.l; u++) {
+        const uint32_t sh = u * A.log2B;
+        const uint32_t mask = u + 1 == A.l ? 0xffffu : (1u << A.log2B) - 1;
+        v4i x;
+#pragma unroll
+        for (int g = 0; g < 4; g++) {
+            // two fields, minus B/2, as two balanced bytes each: + 0x80, low byte xor 0x80
+            const uint32_t f0 = ((uint32_t)(y[2 * g] >> sh) & mask) + A.mx.bias16;
+            const uint32_t f1 = ((uint32_t)(y[2 * g + 1] >> sh) & mask) + A.mx.bias16;
+            x[g] = (int32_t)(((f0 & 0xffffu) | (f1 << 16)) ^ 0x00800080u);
+        }
+        dig[(u * NB + b) * 64 + lane] = x;
+    }
+    if (A.l & 1) dig[(A.l * NB + b) * 64 + lane] = v4i{};  // the last pair's second polynomial
+}
+
+// The last inverse stage of one prime for output tile `tile` of P parts: z(p, block) the tiles'
+// values as operands, ia the tile's constants in memory.  Constants in groups of four blocks,
+// each group requested before the one in hand is used.
+template <int P, int NL, class Z>
+__device__ __forceinline__ void mx_wide_last(const v4i *ia, uint32_t pos, Z z, int32_t (&lo)[P][16], int32_t (&hi)[P][16])
+{
+    constexpr int T1 = MxWide::T1;
+    v4i kc[2][8];
+    auto request = [&](int g) {
+        const int jj = g / T1;
+#pragma unroll
+        for (int b = 0; b < 4; b++)
+#pragma unroll
+            for (int j = 0; j < (jj ? NL - 2 : 2); j++)
+                kc[g & 1][2 * b + j] = ia[(NL * (4 * (g % T1) + b) + 2 * jj + j) * 64 + pos];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    request(0);
+    v16i c[P][2];
+#pragma unroll
+    for (int g = 0; g < 2 * T1; g++) {
+        const int jj = g / T1;
+        if (g + 1 < 2 * T1) request(g + 1);
+        if (g % T1 == 0) {
+#pragma unroll
+            for (int p = 0; p < P; p++) c[p][0] = c[p][1] = v16i{};
+        }
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+            v4i x[P];
+#pragma unroll
+            for (int p = 0; p < P; p++) x[p] = z(p, 4 * (g % T1) + b);
+#pragma unroll
+            for (int j = 0; j < (jj ? NL - 2 : 2); j++)
+#pragma unroll
+                for (int p = 0; p < P; p++) c[p][j] = mfma(kc[g & 1][2 * b + j], x[p], c[p][j]);
+        }
+        if (g % T1 == T1 - 1) {
+#pragma unroll
+            for (int p = 0; p < P; p++) mx_join<NL>(jj, c[p][0], c[p][1], jj ? hi[p] : lo[p]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// to = from + the coefficients lo + 2^16 hi of one part and tile (to and from at the tile).
+__device__ __forceinline__ void mx_wide_store(const uint32_t *from, uint32_t *to, uint32_t pos, const int32_t (&lo)[16],
+                                              const int32_t (&hi)[16], int32_t two32, int32_t two48, const ModS &m)
+{
+    const uint32_t at = 128 * (pos >> 5) + (pos & 31), Q = (uint32_t)m.Q;
+    uint32_t old[16];
+#pragma unroll
+    for (int v = 0; v < 16; v++) old[v] = from[at + mx_off(v)];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        int64_t s4[4];
+        int32_t o[4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) s4[s] = (int64_t)lo[4 * q + s] * two32 + (int64_t)hi[4 * q + s] * two48;
+        redc4(s4, m, o);
+#pragma unroll
+        for (int s = 0; s < 4; s++)  // o in (-Q, Q)
+            to[at + mx_off(4 * q + s)] = add_q(old[4 * q + s], min((uint32_t)o[s], (uint32_t)o[s] + Q), Q);
+    }
+}
+
 // A barrier among the waves of one component: the other components of the workgroup go
 // their own pace, so that one's digits (memory latency, vector work) run beside another's
 // products.  Every wave of the component arrives, all are resident: the wait ends.
@@ -739,51 +867,11 @@ __device__ __forceinline__ void mx_wide_run(const WideArgs &A, uint32_t num_task
             __asm__ volatile("" ::"v"(touched));
             sync();  // the previous digits (at first: tiles) are read
             if (active) {
-                // element e: coefficient 32 i1 + col, i1 = 16 wi + 8 half + e
+                MxWords wd;
                 const WideRow w = wide_row(key == 0 ? (M - am) % M : am, r, comp, N);
-                const uint32_t *o = own + part * PW, *s = ct_acc + (size_t)w.src * CW + part * PW;
-                const uint32_t at = 32 * (16 * wi + 8 * half) + col;
-                // every word is requested before the first is used
-                uint32_t vo[2][E], vs[2][E];
-#pragma unroll
-                for (int p = 0; p < 2; p++)
-#pragma unroll
-                    for (int e = 0; e < E; e++) {
-                        vo[p][e] = o[p * N + at + 32 * e];
-                        vs[p][e] = s[p * N + ((at + 32 * e - w.e) & (N - 1))];
-                    }
+                mx_wide_request(wd, own + part * PW, ct_acc + (size_t)w.src * CW + part * PW, w, wi, lane);
                 __builtin_amdgcn_sched_barrier(0);
-                auto flips = [&](int e) { return (at + 32 * e < w.e) != w.neg; };
-                const ModQ m1{A.Q[1], A.qn[1]};
-                const uint64_t hw = (A.Qw - 1) / 2;
-                uint64_t y[E];
-#pragma unroll
-                for (int e = 0; e < E; e++) {
-                    auto diff = [&](int p) {
-                        const uint32_t v = vs[p][e], Qp = A.Q[p];
-                        return sub_q(flips(e) && v ? Qp - v : v, vo[p][e], Qp);
-                    };
-                    const uint32_t a0 = diff(0), a1 = diff(1);
-                    // x = a0 + Q0 ((a1 - a0) Q0^-1 mod Q1), in [0, Q0 Q1)
-                    const uint64_t x = a0 + (uint64_t)A.Q[0] * mont_mul(a1 + A.crt_cq - a0, A.crt_inv, m1);
-                    int64_t xc = x > hw ? (int64_t)(x - A.Qw) : (int64_t)x;
-                    if (A.sg) xc = (xc + (1ll << (A.sg - 1))) >> A.sg;
-                    y[e] = (uint64_t)xc + A.goff;
-                }
-                for (uint32_t u = 0; u < A.l; u++) {
-                    const uint32_t sh = u * A.log2B;
-                    const uint32_t mask = u + 1 == A.l ? 0xffffu : (1u << A.log2B) - 1;
-                    v4i d;
-#pragma unroll
-                    for (int g = 0; g < 4; g++) {
-                        // two fields, minus B/2, as two balanced bytes each: + 0x80, low byte xor 0x80
-                        const uint32_t f0 = ((uint32_t)(y[2 * g] >> sh) & mask) + A.mx.bias16;
-                        const uint32_t f1 = ((uint32_t)(y[2 * g + 1] >> sh) & mask) + A.mx.bias16;
-                        d[g] = (int32_t)(((f0 & 0xffffu) | (f1 << 16)) ^ 0x00800080u);
-                    }
-                    dig[(u * NB + wi) * 64 + lane] = d;
-                }
-                if (A.l & 1) dig[(A.l * NB + wi) * 64 + lane] = v4i{};  // the last pair's second polynomial
+                mx_wide_digits(wd, w, wi, A, lane, dig);
             }
             sync();  // the digits are written
             if (active) {
@@ -842,60 +930,11 @@ __device__ __forceinline__ void mx_wide_run(const WideArgs &A, uint32_t num_task
         uint32_t pos = lane;  // opaque: the addresses below are not carried through the products
         __asm__("" : "+v"(pos));
         const v4i *const ia = mem + (C::IA + 4 * NL * T1 * tile) * 64;
-        // constants in groups of four blocks, each group requested before the one in hand is used
-        constexpr int GROUPS = 2 * T1;
-        v4i kc[2][8];
-        auto request = [&](int g) {
-            const int jj = g / T1;
-#pragma unroll
-            for (int b = 0; b < 4; b++)
-#pragma unroll
-                for (int j = 0; j < (jj ? NL - 2 : 2); j++)
-                    kc[g & 1][2 * b + j] = ia[(NL * (4 * (g % T1) + b) + 2 * jj + j) * 64 + pos];
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        request(0);
-        v16i c[2][2];
-#pragma unroll
-        for (int g = 0; g < GROUPS; g++) {
-            const int jj = g / T1;
-            if (g + 1 < GROUPS) request(g + 1);
-            if (g % T1 == 0) c[0][0] = c[0][1] = c[1][0] = c[1][1] = v16i{};
-#pragma unroll
-            for (int b = 0; b < 4; b++) {
-                const v4i x1 = swap[(4 * (g % T1) + b) * 64 + lane];
-#pragma unroll
-                for (int j = 0; j < (jj ? NL - 2 : 2); j++) {
-                    c[0][j] = mfma(kc[g & 1][2 * b + j], x0[4 * (g % T1) + b], c[0][j]);
-                    c[1][j] = mfma(kc[g & 1][2 * b + j], x1, c[1][j]);
-                }
-            }
-            if (g % T1 == T1 - 1) {
-#pragma unroll
-                for (int p = 0; p < 2; p++) mx_join<NL>(jj, c[p][0], c[p][1], jj ? hi[p] : lo[p]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        const uint32_t at = 128 * (pos >> 5) + (pos & 31);
+        mx_wide_last<2, NL>(ia, pos, [&](int p, int b) { return p ? swap[b * 64 + lane] : x0[b]; }, lo, hi);
 #pragma unroll
         for (int part = 0; part < 2; part++) {
-            const uint32_t *const from = own + part * PW + pr * N + 1024 * tile;
-            uint32_t *const to = wr + part * PW + pr * N + 1024 * tile;
-            uint32_t old[16];
-#pragma unroll
-            for (int v = 0; v < 16; v++) old[v] = from[at + mx_off(v)];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                int32_t o[4];
-#pragma unroll
-                for (int s = 0; s < 4; s++)
-                    s4[s] = (int64_t)lo[part][4 * q + s] * X.two32 + (int64_t)hi[part][4 * q + s] * two48;
-                redc4(s4, m, o);
-#pragma unroll
-                for (int s = 0; s < 4; s++)  // o in (-Q, Q)
-                    to[at + mx_off(4 * q + s)] = add_q(old[4 * q + s], min((uint32_t)o[s], (uint32_t)o[s] + Q), Q);
-            }
+            const size_t at = part * PW + pr * N + 1024 * tile;
+            mx_wide_store(own + at, wr + at, pos, lo[part], hi[part], X.two32, two48, m);
         }
     }
 }
@@ -915,6 +954,152 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         mx_wide_run<KEYS, 3>(A, num_tasks, cst, digits, arrive);
     else
         mx_wide_run<KEYS, 4>(A, num_tasks, cst, digits, arrive);
+}
+
+// Light work: one workgroup per component and prime (work item 2 task + prime), eight waves.
+// Wave (g, part, tile): with a ternary secret g is the key, else every other pair of digits; it
+// forms KEYS of the part's contraction blocks of the digits, runs its pairs onto both parts'
+// sums of its tile, and the sums meet in the waves g = 0, which run the inverse of
+// their part and tile.  LDS: one prime's constants, the digits of every key and part, and in
+// their place the sums and the tiles.
+//
+// Bound by the chain of one step (about 13 us of digits, two pairs of products, three
+// exchanges and the inverse, 6 of launch): at n = 512, ternary, 16 components take 9.5 ms and 128 9.9,
+// against 17.6 for the butterfly workgroups of two digit groups (35 us a step) and 26.3 for four
+// waves per component.
+template <int KEYS, int NL>
+__device__ __forceinline__ void mx_wide_split_run(const WideArgs &A, const WideTask &T, const v4i *cst, v4i *area)
+{
+    using C = MxWide;
+    constexpr int T1 = C::T1, N = C::N, NB = C::NB, pr = NL == 3 ? 1 : 0;
+    constexpr size_t PW = (size_t)2 * N, CW = 2 * PW;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = wave >> 2, part = (wave >> 1) & 1, tile = wave & 1;
+    const uint32_t i = T.i0 + A.step, r = T.r, comp = T.comp;
+    const uint32_t *const ct_acc = A.acc_rd + T.acc_off, *const own = ct_acc + (size_t)comp * CW;
+    uint32_t *const wr = A.acc_wr + T.acc_off + (size_t)comp * CW;
+    const ModS m{(int32_t)A.Q[pr], A.qn[pr]};
+    MxArgs X = A.mx;
+    X.two32 = pr ? A.mx.two32_1 : A.mx.two32;
+    const int neg = ((32 - lane) & 31) | (lane & 32);
+    const int key = KEYS == 2 ? g : 0;
+    v4i *const dig = area + (2 * key + part) * MX_MAX_L * NB * 64;
+    {
+        const uint32_t M = 2u * N * r;
+        const uint32_t am =
+            __builtin_amdgcn_readfirstlane(modswitch_dev(A.ct_in[(size_t)T.ct * A.ct_stride + i], T.q_in, M));
+        const WideRow w = wide_row(key == 0 ? (M - am) % M : am, r, comp, N);
+        const uint32_t *const src = ct_acc + (size_t)w.src * CW + part * PW;
+        MxWords wd[KEYS];
+#pragma unroll
+        for (int j = 0; j < KEYS; j++) mx_wide_request(wd[j], own + part * PW, src, w, KEYS == 2 ? 2 * tile + j : 2 * tile + g, lane);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < KEYS; j++) mx_wide_digits(wd[j], w, KEYS == 2 ? 2 * tile + j : 2 * tile + g, A, lane, dig);
+    }
+    __syncthreads();  // digits and constants are written
+    int64_t acc[2][16];
+#pragma unroll
+    for (int v = 0; v < 16; v++) acc[0][v] = acc[1][v] = 0;
+    const uint32_t pairs = (A.l + 1) / 2;
+    const v4i *K = reinterpret_cast<const v4i *>(A.mx.bsk) + (((size_t)i * KEYS + key) * 2 + pr) * (A.l * N) +
+                   (size_t)(part ? 0 : A.l) * (N / 2) + tile * 256;
+#pragma unroll 1
+    for (uint32_t k = KEYS == 2 ? 0 : g; k < pairs; k += KEYS == 2 ? 1 : 2) {
+        __asm__ volatile("" ::: "memory");
+        const uint32_t u1 = min(2 * k + 1, A.l - 1);
+        const v4i *const kr[2] = {K + (size_t)(2 * k) * (N / 2), K + (size_t)u1 * (N / 2)};
+        mx_wide_pair<NB, NL>(dig + 2 * k * NB * 64, dig + (2 * k + 1) * NB * 64, cst + tile * NB * NL * 64,
+                             cst + C::fb(NL) * 64, cst + (C::twf(NL) + 8 * tile) * 64, kr, N / 4, lane, X, m, acc);
+    }
+    mx_fold(acc, X);  // four waves' sums of up to four products each then stay below 2^63
+    auto send = [&](v4i *to, const int64_t (&t)[16]) {
+#pragma unroll
+        for (int v = 0; v < 8; v++)
+            to[v * 64 + lane] = v4i{(int32_t)t[2 * v], (int32_t)(t[2 * v] >> 32), (int32_t)t[2 * v + 1],
+                                    (int32_t)(t[2 * v + 1] >> 32)};
+    };
+    auto receive = [&](const v4i *from, int64_t (&t)[16]) {
+#pragma unroll
+        for (int v = 0; v < 8; v++) {
+            const v4i x = from[v * 64 + lane];
+            t[2 * v] += (int64_t)((uint64_t)(uint32_t)x[1] << 32 | (uint32_t)x[0]);
+            t[2 * v + 1] += (int64_t)((uint64_t)(uint32_t)x[3] << 32 | (uint32_t)x[2]);
+        }
+    };
+    __syncthreads();  // the digits are read
+    if (g == 1) {
+        send(area + (wave & 3) * 1024, acc[0]);
+        send(area + (wave & 3) * 1024 + 512, acc[1]);
+    }
+    __syncthreads();
+    int64_t sum[16];
+    if (g == 0) {
+        receive(area + wave * 1024, acc[0]);
+        receive(area + wave * 1024 + 512, acc[1]);
+        __asm__ volatile("" ::: "memory");
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+            sum[v] = part ? acc[1][v] : acc[0][v];
+            acc[0][v] = part ? acc[0][v] : acc[1][v];
+        }
+        send(area + wave * 1024, acc[0]);  // the other part's, in the place this wave alone has read
+    }
+    __syncthreads();
+    int32_t lo[1][16], hi[1][16];
+    v4i z[4];
+    const v4i *const mem = reinterpret_cast<const v4i *>(A.mx.cst) + (size_t)C::mem(pr) * 64;
+    if (g == 0) {
+        receive(area + (wave ^ 2) * 1024, sum);
+        int64_t s4[4];
+        v4i ti[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) ti[j] = mem[(8 * tile + j) * 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; q++) mx_cut(q, sum, X, m, s4, z);
+        mx_stage<false, NL>(cst + C::fb(NL) * 64, z, neg, lo[0], hi[0], [](int) {});
+#pragma unroll
+        for (int t = 0; t < 8; t++) mx_twist(t, lo[0], hi[0], ti, 1, X, m, s4, z);
+    }
+    __syncthreads();  // the sums are read
+    v4i *const tiles = area + part * 8 * 64;
+    if (g == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) tiles[(4 * tile + q) * 64 + lane] = z[q];
+    }
+    __syncthreads();
+    if (g == 1) return;
+    uint32_t pos = lane;
+    __asm__("" : "+v"(pos));
+    mx_wide_last<1, NL>(mem + (C::IA + 4 * NL * T1 * tile) * 64, pos, [&](int, int b) { return tiles[b * 64 + lane]; }, lo, hi);
+    const size_t at = part * PW + pr * N + 1024 * tile;
+    mx_wide_store(own + at, wr + at, pos, lo[0], hi[0], X.two32, pr ? A.mx.two48_1 : A.mx.two48, m);
+}
+
+template <int KEYS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_wide_split(WideArgs A)
+{
+    using C = MxWide;
+    __shared__ v4i cst[C::lds_ops(4) * 64];
+    __shared__ v4i area[4 * 1024];  // digits [key][part][u][block], then sums, then tiles
+    static_assert(2 * 2 * MX_MAX_L * C::NB * 64 <= 4 * 1024, "digits of two keys");
+    const uint32_t item = xcd_item(blockIdx.x, gridDim.x);
+    const WideTask T = A.tasks[item / 2];
+    const int pr = item & 1;
+    if (T.i0 + A.step >= A.n) {  // past step n - 1: carried over
+        const size_t off = T.acc_off + (size_t)T.comp * 4 * C::N + (size_t)pr * C::N;
+        for (uint32_t w = threadIdx.x; w < 2u * C::N; w += 512) {
+            const size_t at = off + (size_t)(w / C::N) * 2 * C::N + w % C::N;
+            A.acc_wr[at] = A.acc_rd[at];
+        }
+        return;
+    }
+    const v4i *src = reinterpret_cast<const v4i *>(A.mx.cst) + (pr ? C::lds_ops(4) * 64 : 0);
+    const int ops = pr ? C::lds_ops(3) : C::lds_ops(4);
+    for (int t = threadIdx.x; t < ops * 64; t += 512) cst[t] = src[t];
+    if (pr) mx_wide_split_run<KEYS, 3>(A, T, cst, area);
+    else mx_wide_split_run<KEYS, 4>(A, T, cst, area);
 }
 
 // The bootstrapping key in these kernels' order: dst[poly][tile][q][lane][s], entry of
@@ -970,6 +1155,12 @@ void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint3
     const uint32_t grid = std::min<uint32_t>((num_tasks + waves - 1) / waves, A.mx.num_cu);
     if (keys == 2) hipLaunchKernelGGL(k_mx_step<2>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
     else hipLaunchKernelGGL(k_mx_step<1>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
+}
+
+void launch_mx_split(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st)
+{
+    if (keys == 2) hipLaunchKernelGGL(k_mx_wide_split<2>, dim3(2 * num_tasks), dim3(512), 0, st, A);
+    else hipLaunchKernelGGL(k_mx_wide_split<1>, dim3(2 * num_tasks), dim3(512), 0, st, A);
 }
 
 bool mx_supports(uint32_t N, int npr) { return N == (npr == 2 ? 2048u : 1024u); }

@@ -633,6 +633,7 @@ void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uin
     }
     if (ps && npr == 2) {
         if (dg == 2 && N == 1024) ps_launch<1024, 2, 2>(keys, A, num_tasks, st);
+        else if (dg == 2 && N == 2048 && A.mx.cst) launch_mx_split(keys, A, num_tasks, st);
         else if (dg == 2 && N == 2048) ps_launch<2048, 2, 2>(keys, A, num_tasks, st);
         else {
 #define P_(n, p) ps_launch<n, p>(keys, A, num_tasks, st)
