@@ -1256,8 +1256,11 @@ void run_external_product(mm_ctx &c, uint32_t i, const uint32_t *in, size_t coun
     const size_t words = count * 2 * c.p.N;
     const uint32_t *din = stage_in(d, WS_IN, in, words, dptr, st);
     uint32_t *dout = stage_out(d, WS_OUT, out, words, dptr);
-    dev::launch_external_product(c.p.N, din, dout, count, d.bsk + (size_t)i * 4 * c.p.l * c.p.N, d.twf, d.twi, c.p.Q,
-                                 d.qn, c.p.log2_B, c.p.l, c.sg, st);
+    if (d.mx_cst)
+        dev::launch_mx_product(mx_args(c, d), din, dout, count, i, c.p.Q, d.qn, c.p.log2_B, c.p.l, c.sg, st);
+    else
+        dev::launch_external_product(c.p.N, din, dout, count, d.bsk + (size_t)i * 4 * c.p.l * c.p.N, d.twf, d.twi,
+                                     c.p.Q, d.qn, c.p.log2_B, c.p.l, c.sg, st);
     HIPC(hipGetLastError());
     finish_out(out, dout, words, dptr, st);
 }

@@ -177,6 +177,9 @@ void launch_mx_rotate(const BrArgs &A, int grid, hipStream_t st, int wpp);
 void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
 // (two primes, N = 2048: one workgroup per component and prime)
 void launch_mx_split(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st);
+// External products with RGSW key `key` (launch_external_product; N = 1024, X.cst given).
+void launch_mx_product(const MxArgs &X, const uint32_t *in, uint32_t *out, size_t count, uint32_t key, uint32_t Q,
+                       uint32_t qn, uint32_t log2B, uint32_t l, uint32_t sg, hipStream_t st);
 bool mx_supports(uint32_t N, int npr);
 // polys polynomials of one prime's NTT-domain key (bit-reversed, x 2^32 / N) into the order and
 // scale of MxArgs::bsk; the prime's polynomials are blocks of `block` every primes * block

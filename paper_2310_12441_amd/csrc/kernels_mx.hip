@@ -339,6 +339,31 @@ __device__ __forceinline__ void mx_fold(int64_t (&acc)[2][16], const MxArgs &X)
             acc[p][v] = (int64_t)(int32_t)(acc[p][v] >> 32) * X.two32 + (int64_t)(uint64_t)(uint32_t)acc[p][v];
 }
 
+// Two waves per component: the sums of the other part to its wave, through LDS, ...
+__device__ __forceinline__ void mx_give(const int64_t (&acc)[2][16], int part, int lane, v4i *sums)
+{
+#pragma unroll
+    for (int v = 0; v < 8; v++) {
+        const int64_t t0 = part ? acc[0][2 * v] : acc[1][2 * v];
+        const int64_t t1 = part ? acc[0][2 * v + 1] : acc[1][2 * v + 1];
+        sums[v * 64 + lane] = v4i{(int32_t)t0, (int32_t)(t0 >> 32), (int32_t)t1, (int32_t)(t1 >> 32)};
+    }
+}
+
+// ... and, a barrier later, this part's sums of both waves.
+__device__ __forceinline__ void mx_take(const int64_t (&acc)[2][16], int part, int lane, const v4i *sums,
+                                        int64_t (&mine)[16])
+{
+#pragma unroll
+    for (int v = 0; v < 8; v++) {
+        const v4i t = sums[v * 64 + lane];
+        const int64_t t0 = (int64_t)((uint64_t)(uint32_t)t[1] << 32 | (uint32_t)t[0]);
+        const int64_t t1 = (int64_t)((uint64_t)(uint32_t)t[3] << 32 | (uint32_t)t[2]);
+        mine[2 * v] = (part ? acc[1][2 * v] : acc[0][2 * v]) + t0;
+        mine[2 * v + 1] = (part ? acc[1][2 * v + 1] : acc[0][2 * v + 1]) + t1;
+    }
+}
+
 // The digit fields of D = src - own, or Q - src - own where the rotation negates src (flip
 // all ones): one min brings it to [0, Q), another moves the values above (Q - 1) / 2 below 0
 // (offset by (Q - 1) / 2), and centring, rounding and digit offset are one constant before
@@ -454,13 +479,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     if (KEYS == 2 && key == 0) mx_fold(acc, A.mx);
                 }
                 if constexpr (W == 2) {
-                    // the other part's sums to its wave
-#pragma unroll
-                    for (int v = 0; v < 8; v++) {
-                        const int64_t t0 = p0 ? acc[0][2 * v] : acc[1][2 * v];
-                        const int64_t t1 = p0 ? acc[0][2 * v + 1] : acc[1][2 * v + 1];
-                        sums[wave][v * 64 + lane] = v4i{(int32_t)t0, (int32_t)(t0 >> 32), (int32_t)t1, (int32_t)(t1 >> 32)};
-                    }
+                    mx_give(acc, p0, lane, sums[wave]);
                 }
             }
             __syncthreads();  // every rotation of the step has read the accumulators
@@ -473,14 +492,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     mx_inverse(acc, cst, lane, A.mx, m, store);
                 } else {
                     int64_t mysum[16];
-#pragma unroll
-                    for (int v = 0; v < 8; v++) {
-                        const v4i t = sums[wave ^ 1][v * 64 + lane];
-                        const int64_t t0 = (int64_t)((uint64_t)(uint32_t)t[1] << 32 | (uint32_t)t[0]);
-                        const int64_t t1 = (int64_t)((uint64_t)(uint32_t)t[3] << 32 | (uint32_t)t[2]);
-                        mysum[2 * v] = (p0 ? acc[1][2 * v] : acc[0][2 * v]) + t0;
-                        mysum[2 * v + 1] = (p0 ? acc[1][2 * v + 1] : acc[0][2 * v + 1]) + t1;
-                    }
+                    mx_take(acc, p0, lane, sums[wave ^ 1], mysum);
                     mx_inverse_part(mysum, cst, lane, A.mx, m, [&](int v, uint32_t x) { store(0, v, x); });
                 }
             }
@@ -507,6 +519,66 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         }
         __syncthreads();  // the next group's accumulators take this one's place
+    }
+}
+
+// ------------------------------------------------------------------ external products
+
+// g^{-1}(in) x one key of `count` pairs [count][2][N] -> out: the step without a rotation, W
+// waves per pair as in k_mx_rotate, four pairs per workgroup, the key words shared by all.
+//
+// Bound by the chain of one wave (as a step of k_mx_rotate) up to one workgroup per compute
+// unit, by vector issue beyond.  Measured against k_external_product<1024>: 1 pair 10.2 us
+// against 24.9, 1000 15.5 against 31.3 (1.05 TB/s of pairs read and written), 4096 51.8 against
+// 92.3, 20,000 238 against 389.  With one wave per pair two workgroups share a compute unit
+// and one's loads run under the other's arithmetic (workgroups of eight pairs: 4096 in 56.3 us).
+template <int W>
+__global__ __launch_bounds__(256 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_product(
+    MxArgs X, const uint32_t *in, uint32_t *out, size_t count, uint32_t key, uint32_t Q, uint32_t qn, uint32_t log2B,
+    uint32_t l, uint32_t sg)
+{
+    constexpr int P = 2 / W;
+    __shared__ v4i cst[MX_VECS];
+    __shared__ v4i digits[4 * W][MX_MAX_L * P * 64];
+    __shared__ v4i sums[W == 2 ? 8 : 1][8 * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int base = (lane & 31) + 128 * (lane >> 5), p0 = W == 2 ? wave & 1 : 0;
+    const size_t item = (size_t)blockIdx.x * 4 + wave / W;
+    const bool has = item < count;
+    v4i *const dig = digits[wave];
+    const ModS m{(int32_t)Q, qn};
+    const size_t at = (has ? item : 0) * 2 * MXN + p0 * MXN + base;
+    uint32_t x[P][16];
+#pragma unroll
+    for (int p = 0; p < P; p++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) x[p][v] = in[at + p * MXN + mx_off(v)];
+    for (int t = threadIdx.x; t < MX_VECS; t += 256 * W) cst[t] = reinterpret_cast<const v4i *>(X.cst)[t];
+    __syncthreads();
+    int64_t acc[2][16];
+    if (has) {
+#pragma unroll
+        for (int p = 0; p < P; p++)
+#pragma unroll
+            for (int v = 0; v < 16; v++) x[p][v] = mx_field(x[p][v], 0, 0, 0, Q, X, sg);
+        mx_digits<P>(x, l, log2B, X, lane, dig);
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[0][v] = acc[1][v] = 0;
+        const int32_t *K = X.bsk + (size_t)key * (4u * l * MXN);
+        if constexpr (W == 1) mx_products(dig, cst, K, l, lane, X, m, acc);
+        else mx_products_part(dig, p0, cst, K, l, lane, X, m, acc);
+    }
+    auto store = [&](int p, int v, uint32_t c) { out[at + p * MXN + mx_off(v)] = c; };
+    if constexpr (W == 1) {
+        if (has) mx_inverse(acc, cst, lane, X, m, store);
+    } else {
+        if (has) mx_give(acc, p0, lane, sums[wave]);
+        __syncthreads();
+        if (has) {
+            int64_t mysum[16];
+            mx_take(acc, p0, lane, sums[wave ^ 1], mysum);
+            mx_inverse_part(mysum, cst, lane, X, m, [&](int v, uint32_t c) { store(0, v, c); });
+        }
     }
 }
 
@@ -1155,6 +1227,17 @@ void launch_mx_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint3
     const uint32_t grid = std::min<uint32_t>((num_tasks + waves - 1) / waves, A.mx.num_cu);
     if (keys == 2) hipLaunchKernelGGL(k_mx_step<2>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
     else hipLaunchKernelGGL(k_mx_step<1>, dim3(grid), dim3(64 * waves), 0, st, A, num_tasks);
+}
+
+void launch_mx_product(const MxArgs &X, const uint32_t *in, uint32_t *out, size_t count, uint32_t key, uint32_t Q,
+                       uint32_t qn, uint32_t log2B, uint32_t l, uint32_t sg, hipStream_t st)
+{
+    // two waves per pair while one round of workgroups (one per compute unit) takes them all: 1024
+    // pairs 15.6 us; the next pair would cost a second round, 1025 pairs take 23.6 us with one
+    const bool two = count <= 4 * X.num_cu;
+    const dim3 grid((uint32_t)((count + 3) / 4));
+    if (two) hipLaunchKernelGGL(k_mx_product<2>, grid, dim3(512), 0, st, X, in, out, count, key, Q, qn, log2B, l, sg);
+    else hipLaunchKernelGGL(k_mx_product<1>, grid, dim3(256), 0, st, X, in, out, count, key, Q, qn, log2B, l, sg);
 }
 
 void launch_mx_split(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st)

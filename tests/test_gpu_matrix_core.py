@@ -148,3 +148,29 @@ def test_two_primes_2048(l, log2_B, ternary):
     ctx.set_schedule(ids, shapes[5])
     np.testing.assert_array_equal(ctx.bootstrap(ids, cts), out)
     ctx.close()
+
+
+@pytest.mark.parametrize("l,log2_B,ternary,Q", [(1, 7, False, 0), (3, 6, True, 0), (4, 7, False, 0), (4, 7, True, 12289)])
+def test_external_products(l, log2_B, ternary, Q):
+    """One external product per pair of waves and per wave (more than four per compute unit),
+    with part-filled workgroups at the end, and the coefficients where rounding and centring turn."""
+    p = replace(Params(n=2, N=N, log2_B=log2_B, l=l), ternary=ternary)
+    if Q:
+        p = replace(p, Q=Q)
+    ctx, keys = _context(p, 2500 + l)
+    rng = np.random.default_rng(l)
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    pairs = rng.integers(0, p.Q, (4 * cus + 9, 2, N), dtype=np.uint32)
+    edges = np.array([0, 1, p.Q // 2 - 1, p.Q // 2, p.Q // 2 + 1, p.Q - 2, p.Q - 1], np.uint32)
+    pairs[0] = edges[rng.integers(0, len(edges), (2, N))]
+    pairs[-1] = p.Q // 2
+    i = len(keys.bsk) - 1
+    for count in (1, 7, len(pairs)):
+        sub = pairs[-count:].copy()
+        sub[0] = pairs[0]
+        got = ctx.external_product(i, sub)
+        for k in {0, count // 2, count - 1}:
+            np.testing.assert_array_equal(got[k], oracle.external_product(keys.bsk[i], sub[k], p.Q, log2_B, l),
+                                          err_msg=f"count {count} item {k}")
+    ctx.close()
