@@ -253,6 +253,13 @@ static std::vector<uint32_t> mx_tables(const mm_ctx &c)
                 for (int m = 0; m < 4; m++) {
                     const int32_t w = centred(mulmod(at(64 * row * col), (uint32_t)((1ull << (8 * m)) % Q), Q), Q);
                     for (int j = 0; j < 4; j++) put(4 + 4 * (int)q + j, lane, 4 * s + m, balanced_byte(w, j));
+                    // the first stage for residues, likewise (behind the 28 operands, 16 row
+                    // factors and 8 inverse twiddles)
+                    const int32_t a = centred(mulmod(at(32 * row * (2 * col + 1)), (uint32_t)((1ull << (8 * m)) % Q), Q), Q);
+                    for (int j = 0; j < 4; j++) {
+                        const size_t o = ((size_t)(36 + 4 * q + j) * 64 + 16 + lane) * 4;
+                        out[o + s] |= balanced_byte(a, j) << (8 * m);
+                    }
                 }
                 // twiddles of the value at (row, column): forward (i2, k1), inverse (k1, i2);
                 // factors of the last inverse stage's rows i1
@@ -580,6 +587,8 @@ dev::MxArgs mx_args(const mm_ctx &c, const Device &d)
     };
     shifts(p.Q, X.two32, X.two48);
     if (c.wide) shifts(p.Q2, X.two32_1, X.two48_1);
+    X.ring = centred(to_mont(d.c_fix, p.Q), p.Q);
+    X.ring16 = centred(mulmod(to_mont(d.c_fix, p.Q), 65536 % p.Q, p.Q), p.Q);
     X.num_cu = (uint32_t)d.num_cu;
     return X;
 }
@@ -1277,7 +1286,10 @@ void run_negacyclic_mul(mm_ctx &c, const uint32_t *a, const uint32_t *b, size_t 
     const uint32_t *da = stage_in(d, WS_IN, a, words, dptr, st);
     const uint32_t *db = stage_in(d, WS_IN2, b, words, dptr, st);
     uint32_t *dout = stage_out(d, WS_OUT, out, words, dptr);
-    dev::launch_negacyclic_mul(c.p.N, da, db, dout, count, d.twf, d.twi, c.p.Q, d.qn, d.c_fix, st);
+    if (d.mx_cst && !c.wide)
+        dev::launch_mx_ring(mx_args(c, d), da, db, dout, count, c.p.Q, d.qn, st);
+    else
+        dev::launch_negacyclic_mul(c.p.N, da, db, dout, count, d.twf, d.twi, c.p.Q, d.qn, d.c_fix, st);
     HIPC(hipGetLastError());
     finish_out(out, dout, words, dptr, st);
 }

@@ -33,7 +33,7 @@ struct WaveTask {
 
 // The matrix-core kernels (kernels_mx.hip): N = 1024 at one prime with digits of at most 7 bits,
 // N = 2048 at two primes (the second below 2^24) with digits of at most 15 bits.
-constexpr uint32_t MX_CONST_WORDS = (36 * 64 + 16) * 4;  // words of the constant block of N = 1024
+constexpr uint32_t MX_CONST_WORDS = (52 * 64 + 16) * 4;  // words of the constant block of N = 1024
 // of N = 2048, operands of 256 words: per prime the first stage's 2 x 4 blocks of four limbs
 // (three at the second prime), the second's 4 blocks, 16 of twiddles each way, the last stage's
 // 16 blocks
@@ -50,6 +50,7 @@ struct MxArgs {
     int32_t two16;       // 65536, as an argument so that the compiler keeps the 64-bit multiply-add
     int32_t two32, two48;      // 2^32 and 2^48 mod Q, balanced
     int32_t two32_1, two48_1;  // the same for the second prime
+    int32_t ring, ring16;  // 2^96 / N and 2^112 / N mod Q, balanced (one prime)
     uint32_t num_cu;     // compute units
 };
 
@@ -180,6 +181,9 @@ void launch_mx_split(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipSt
 // External products with RGSW key `key` (launch_external_product; N = 1024, X.cst given).
 void launch_mx_product(const MxArgs &X, const uint32_t *in, uint32_t *out, size_t count, uint32_t key, uint32_t Q,
                        uint32_t qn, uint32_t log2B, uint32_t l, uint32_t sg, hipStream_t st);
+// Ring products (launch_negacyclic_mul; N = 1024, X.cst given).
+void launch_mx_ring(const MxArgs &X, const uint32_t *a, const uint32_t *b, uint32_t *out, size_t count, uint32_t Q,
+                    uint32_t qn, hipStream_t st);
 bool mx_supports(uint32_t N, int npr);
 // polys polynomials of one prime's NTT-domain key (bit-reversed, x 2^32 / N) into the order and
 // scale of MxArgs::bsk; the prime's polynomials are blocks of `block` every primes * block

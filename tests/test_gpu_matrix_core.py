@@ -174,3 +174,28 @@ def test_external_products(l, log2_B, ternary, Q):
             np.testing.assert_array_equal(got[k], oracle.external_product(keys.bsk[i], sub[k], p.Q, log2_B, l),
                                           err_msg=f"count {count} item {k}")
     ctx.close()
+
+
+@pytest.mark.parametrize("Q", [0, 12289, 1073692673])
+def test_ring_products(Q):
+    """Products of polynomials of full-width residues: edges of the centred range, part-filled
+    workgroups, and more products than the grid holds at once."""
+    p = Params(n=2, N=N, log2_B=6 if Q else 7, l=4)
+    if Q:
+        p = replace(p, Q=Q)
+    ctx, _ = _context(p, 2600)
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(p.Q)
+    a, b = rng.integers(0, p.Q, (2, 12 * cus + 5, N), dtype=np.uint32)
+    edges = np.array([0, 1, p.Q // 2, p.Q // 2 + 1, p.Q - 1], np.uint32)
+    a[0], b[0] = edges[rng.integers(0, len(edges), (2, N))]
+    a[-1], b[-1] = p.Q // 2, p.Q - 1
+    a[-2], b[-2] = p.Q // 2 + 1, p.Q // 2 + 1
+    for count in (1, 6, len(a)):
+        x, y = a[-count:].copy(), b[-count:].copy()
+        x[0], y[0] = a[0], b[0]
+        got = ctx.negacyclic_mul(x, y)
+        for k in {0, count // 2, max(0, count - 2), count - 1}:
+            np.testing.assert_array_equal(got[k], oracle.poly_mul(x[k], y[k], p.Q), err_msg=f"count {count} item {k}")
+    ctx.close()
