@@ -69,17 +69,17 @@ constexpr int MX_VECS = MX_FIN * 64 + 16;
 constexpr int MX_FR = MX_VECS + 8 * 64;  // the first stage for residues, [contraction block][limb] (k_mx_ring)
 static_assert((MX_FR + 16 * 64) * 4 == (int)MX_CONST_WORDS, "constant block size");
 
-// A workgroup's copy of ops operands into LDS, four requests per thread in flight.
-template <class Src>
+// A workgroup's copy of ops operands into LDS, DEPTH requests per thread in flight.
+template <int DEPTH = 4, class Src>
 __device__ __forceinline__ void mx_copy(int ops, Src src, v4i *dst)
 {
-    for (int t0 = threadIdx.x; t0 < ops; t0 += 4 * (int)blockDim.x) {
-        v4i x[4];
+    for (int t0 = threadIdx.x; t0 < ops; t0 += DEPTH * (int)blockDim.x) {
+        v4i x[DEPTH];
 #pragma unroll
-        for (int k = 0; k < 4; k++) x[k] = src(min(t0 + k * (int)blockDim.x, ops - 1));
+        for (int k = 0; k < DEPTH; k++) x[k] = src(min(t0 + k * (int)blockDim.x, ops - 1));
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int k = 0; k < 4; k++) dst[min(t0 + k * (int)blockDim.x, ops - 1)] = x[k];
+        for (int k = 0; k < DEPTH; k++) dst[min(t0 + k * (int)blockDim.x, ops - 1)] = x[k];
     }
 }
 
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ v4i digits[8][MX_MAX_L * P * 64];
     __shared__ uint32_t accs[8 / W][2 * MXN];
     __shared__ v4i sums[W == 2 ? 8 : 1][8 * 64];
-    for (int t = threadIdx.x; t < MX_VECS; t += 512) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
+    mx_copy(MX_VECS, [&](int t) { return reinterpret_cast<const v4i *>(A.mx.cst)[t]; }, cst);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int base = (lane & 31) + 128 * (lane >> 5);  // + mx_off(v): the coefficient of register v
     const int slot = wave / W, p0 = W == 2 ? wave & 1 : 0;
@@ -685,7 +685,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 {
     __shared__ v4i cst[MX_VECS];
     __shared__ v4i digits[8][MX_MAX_L * 2 * 64];
-    for (int t = threadIdx.x; t < MX_VECS; t += blockDim.x) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
+    mx_copy<8>(MX_VECS, [&](int t) { return reinterpret_cast<const v4i *>(A.mx.cst)[t]; }, cst);
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t waves = blockDim.x >> 6;
@@ -1114,7 +1114,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     __shared__ uint32_t arrive[C::COMPS];
     static_assert(sizeof(digits) == 8 * 4 * 64 * 16, "one part's tile per wave");
     if (threadIdx.x < C::COMPS) arrive[threadIdx.x] = 0;
-    for (int t = threadIdx.x; t < C::LDS_OPS * 64; t += 512) cst[t] = reinterpret_cast<const v4i *>(A.mx.cst)[t];
+    mx_copy<8>(C::LDS_OPS * 64, [&](int t) { return reinterpret_cast<const v4i *>(A.mx.cst)[t]; }, cst);
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % C::WAVES >= C::T1)
         mx_wide_run<KEYS, 3>(A, num_tasks, cst, digits, arrive);
@@ -1263,7 +1263,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
     const v4i *src = reinterpret_cast<const v4i *>(A.mx.cst) + (pr ? C::lds_ops(4) * 64 : 0);
     const int ops = pr ? C::lds_ops(3) : C::lds_ops(4);
-    for (int t = threadIdx.x; t < ops * 64; t += 512) cst[t] = src[t];
+    mx_copy<8>(ops * 64, [&](int t) { return src[t]; }, cst);
     if (pr) mx_wide_split_run<KEYS, 3>(A, T, cst, area);
     else mx_wide_split_run<KEYS, 4>(A, T, cst, area);
 }
