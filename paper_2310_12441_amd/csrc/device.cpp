@@ -650,6 +650,16 @@ KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
     return k;
 }
 
+// Key switch behind a blind rotation of one launch per step: a few samples by the i-split kernel,
+// which reads only the rows their digits name.  The lane kernel reads the whole key, and the
+// next call's steps, each a launch that starts on the bootstrapping key in memory, run longer
+// for it (call of 1 ciphertext of r = 4 6.37 ms against 6.60, 16 of r = 8 6.65 against 6.80, 24
+// 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).
+static KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count)
+{
+    return count <= 16 ? KsSched{0, ks_splits(c, d, count)} : ks_default(c, d, count);
+}
+
 size_t ks_part_words(const mm_ctx &c, const KsSched &k, size_t count) { return (size_t)k.P * count * (c.p.n + 1); }
 
 // Enqueue key switch + final modulus switch of `count` extracted samples
@@ -849,9 +859,9 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     if (use_global(c, ids, count)) {
         const uint64_t comps = sum_r(c, ids, count);
         if (prime_split(c, d, comps))
-            return Sched{0, ks_default(c, d, count), 0, prime_split_dg(c, d, comps) == 2 ? 6 : 5};
+            return Sched{0, ks_after_steps(c, d, count), 0, prime_split_dg(c, d, comps) == 2 ? 6 : 5};
         const int shape = global_shapes(c).front();
-        return Sched{0, ks_default(c, d, count), shape == 3 ? dev::SPLIT_WAVES : 0, shape};
+        return Sched{0, ks_after_steps(c, d, count), shape == 3 ? dev::SPLIT_WAVES : 0, shape};
     }
     // untuned, at N = 1024 (the ring of the paper-shaped parameters, measured for
     // r = 4 and 8 at 1024 to 16384 components; at N = 512 the fused kernel measured
@@ -878,7 +888,7 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
         (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
-        return Sched{0, ks_default(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};
+        return Sched{0, ks_after_steps(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};
     if (comps <= 4 * cu && two_wave) return Sched{8, ks_default(c, d, count), 2};
     // rings of several waves per component: groups of four waves (two workgroups per compute
     // unit, each its own barriers) where the last round of eight-wave groups would be at most
