@@ -508,13 +508,14 @@ std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uin
     return tasks;
 }
 
-// Components per group for a batch of `comps` components: the full width,
-// or half of it when that still fits every group on its own compute unit.
+// Components per group for a batch of `comps` components: the full width, halved as long as
+// that still fits every group on its own compute unit (two waves per component, r = 1, N =
+// 1024: 100 ciphertexts 4.4 ms one per group, 6.4 four per group; ternary, 20, 7.7 against 11.1).
 uint32_t spread_cap(const Device &d, uint64_t comps, uint32_t gw, uint32_t wpp)
 {
-    const uint32_t slots = gw / wpp;
-    if (slots >= 8 && comps <= (uint64_t)(slots / 2) * (uint64_t)d.num_cu) return slots / 2;
-    return slots;
+    uint32_t cap = gw / wpp;
+    while (cap > 1 && comps <= (uint64_t)(cap / 2) * (uint64_t)d.num_cu) cap /= 2;
+    return cap;
 }
 
 static std::vector<dev::WaveTask> pack_groups(const mm_ctx &c, const Device &d, const int *ids, size_t count,

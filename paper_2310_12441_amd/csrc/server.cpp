@@ -462,7 +462,7 @@ void Server::launch(Part &p)
     const uint32_t wpp = (uint32_t)dev::waves_per_poly(c->p.N);
     uint64_t comps = 0;
     for (auto &a : p.active) comps += c->tables[a.table].r;
-    const uint32_t cap = spread_cap(d, comps, 8, wpp);
+    const uint32_t cap = std::max(spread_cap(d, comps, 8, wpp), std::min(8 / wpp, 4u));
     bool narrow = false, wide = false;
     for (auto &a : p.active) (c->tables[a.table].r > cap ? wide : narrow) = true;
     const uint32_t wide_chunk = narrow && wide ? std::max<uint32_t>(1, chunk * 2 / 3) : chunk;

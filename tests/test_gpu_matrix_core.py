@@ -199,3 +199,19 @@ def test_ring_products(Q):
         for k in {0, count // 2, max(0, count - 2), count - 1}:
             np.testing.assert_array_equal(got[k], oracle.poly_mul(x[k], y[k], p.Q), err_msg=f"count {count} item {k}")
     ctx.close()
+
+
+@pytest.mark.parametrize("rs,count", [((1,), 3), ((1,), 300), ((1, 2, 3), 200)])
+def test_spread_groups(rs, count):
+    """Batches light enough for one or two components per group, an odd remainder and
+    ciphertexts wider than the group's share among them, equal the same one by one."""
+    p = Params(n=4, N=N, log2_B=7, l=4)
+    ctx, keys = _context(p, 2700)
+    tabs = [(r, ctx.table_create(64, 64, r, negacyclic_table(64, 64, 95 + r), 2 * N * 6)) for r in rs]
+    pick = [tabs[j % len(tabs)] for j in range(count)]
+    ed = enc_draws(p.n, 2 * N * 6, count, 9)
+    cts = oracle.encrypt(p.n, 2 * N * 6, 64, keys.s, messages(64, count, 8), ed["a"], ed["e"])
+    ids = np.array([tid for _, tid in pick], np.int32)
+    _fused(ctx, ids, 2)
+    np.testing.assert_array_equal(ctx.bootstrap(ids, cts), ctx.bootstrap(ids, cts, plain=True))
+    ctx.close()
