@@ -777,7 +777,8 @@ int light_global_dg(const mm_ctx &c, const Device &d, uint64_t comps)
 // The matrix-core kernel with two waves per component: see schedule_for.
 bool mx_two_waves(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r)
 {
-    return d.mx_cst && !c.wide && max_r <= 4 && comps <= 4ull * (uint64_t)d.num_cu && (max_r <= 2 || comps > 16);
+    return d.mx_cst && !c.wide && max_r <= 4 && comps <= 4ull * (uint64_t)d.num_cu &&
+           (max_r <= 2 || comps > (c.keys == 2 ? 48u : 16u));
 }
 
 // Two waves per component (N = 512, 1024, r <= 4): for batches that do not
@@ -883,7 +884,8 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     // components per compute unit where every ciphertext fits such slots (148 components 7.0,
     // 400 7.9, 1024 9.2; two digit groups 7.5, 11.0, 19.1; one wave 8.0, 8.8, 9.6; with
     // r <= 2 from the first ciphertext on, 4.2 against 6.1 for one of r = 1; with r = 4
-    // one takes 6.3 either way and up to 16 components keep the digit groups), else one
+    // one takes 6.3 either way and up to 16 components keep the digit groups; with a ternary
+    // secret up to 48, whole calls of r = 4: 20 components 10.8 against 11.1, 64 11.15 either way), else one
     // wave per component above one per compute unit (13.2 for 1600 against 16.2 with two)
     if (mx_two_waves(c, d, comps, two_wave ? max_r(c, ids, count) : 8u)) return Sched{8, ks_default(c, d, count), 2};
     if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};

@@ -10,6 +10,8 @@
 //   Phi(-a'_i) brings to them (an index-and-sign remap, eq. ex1:BPc), form
 //   D = Phi(-a'_i) ACC - ACC, and add D x BSK_i (the binary CMux of
 //   eq. cmux:BP) with a register-resident NTT external product.
+//   Where the matrix-core kernels apply (N = 1024, digits of at most 7 bits) the
+//   eight-wave groups run k_mx_rotate of kernels_mx.hip instead.
 // k_keyswitch / k_ks_finalize: the key switch z -> s (eq. equ-key-swi) and the
 //   final modulus switch Q -> q_out, batched over ciphertexts.
 #include <hip/hip_runtime.h>

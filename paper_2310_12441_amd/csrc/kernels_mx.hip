@@ -1,4 +1,6 @@
-// The CMux step on the matrix cores (one prime below 2^31, N = 1024).
+// The CMux step, the external product and the ring product on the matrix cores: one prime
+// below 2^31 at N = 1024 with digits of at most 7 bits, two primes at N = 2048 with digits of
+// at most 15.
 //
 // The negacyclic NTT of N = 32 x 32 points in two 32-point stages,
 //   X[k1 + 32 k2] = sum_i2 w^(i2 k2) psi^(i2 (2 k1 + 1)) sum_i1 x[32 i1 + i2] psi^(32 i1 (2 k1 + 1)),

@@ -23,8 +23,10 @@
 // components do not fit one workgroup's LDS (r N / 1024 > 8, e.g. r = 16 at
 // N = 1024), for rings of 16384 and more (one polynomial over 16 waves, or the
 // split ring below), which the fused persistent kernel cannot hold, and, with
-// four waves per component at N = 1024, the faster shape for the largest and the
-// lightest batches the fused kernel could hold.  Layouts are the wide ones with the
+// four waves per component at N = 1024, the faster shape for the lightest batches
+// (and, where the matrix-core kernels do not apply, the largest) the fused kernel
+// could hold.  Where the matrix-core kernels of kernels_mx.hip apply they take the
+// place of these steps (launch_wide_step).  Layouts are the wide ones with the
 // prime index dropped: a component is [part][N], key blocks [n][keys][2l][2][N].
 // Variants: two digit groups per workgroup (DG), one workgroup per prime (PS), and
 // an XCD-aware order of work items (xcd_item).
