@@ -39,11 +39,13 @@ SINGLE_ISSUE_LANE_OPS = 256 * 64 * 2.4e9
 MIX_CEILING_LANE_OPS = {2: 38.5e12, 5: 39.7e12}
 PEAK_HBM = 8.0e12
 KERNEL_SOURCES = ("paper_2310_12441_amd/csrc/kernels.hip", "paper_2310_12441_amd/csrc/kernels_wide.hip",
+                  "paper_2310_12441_amd/csrc/kernels_mx.hip", "paper_2310_12441_amd/csrc/rotation_common.hpp",
                   "paper_2310_12441_amd/csrc/device_common.hpp")
-# counter summaries of the two blind-rotation kernels the schedule can pick for the
-# paper-shaped batch: the fused persistent kernel, and the global-accumulator kernel
-# with four waves per component (one launch per CMux step)
-COUNTERS = {"fused": os.path.join(ROOT, "profiles", "k_blind_rotate_paper_shaped_4096_counters.txt"),
+# counter summaries of the blind-rotation kernels the schedule can pick for the
+# paper-shaped batch: the fused persistent kernels (matrix cores, butterflies), and the
+# global-accumulator kernel with four waves per component (one launch per CMux step)
+COUNTERS = {"mx": os.path.join(ROOT, "profiles", "k_mx_rotate_paper_shaped_4096_counters.txt"),
+            "fused": os.path.join(ROOT, "profiles", "k_blind_rotate_paper_shaped_4096_counters.txt"),
             "global": os.path.join(ROOT, "profiles", "k_wide_step_paper_shaped_4096_counters.txt")}
 
 
@@ -253,11 +255,16 @@ def main():
     per_launch = br_avg / launches
     ops = ops_per_bootstrap(p.n, p.N, p.l, r) * B // launches
     achieved = ops / per_launch
+    # eight-wave groups of the lockstep schedule run on the matrix cores where those kernels apply
+    on_matrix = (not global_shape and sched[0] == 8 and sched[5] == 0 and p.N == 1024 and p.log2_B <= 7 and p.l <= 4
+                 and not p.Q2)
     waves_per_simd = 5 if global_shape else 2  # VGPR-bound occupancy of each kernel (94 and 256 VGPRs)
-    mix = MIX_CEILING_LANE_OPS[waves_per_simd]
+    mix = None if on_matrix else MIX_CEILING_LANE_OPS[waves_per_simd]  # a ceiling of the butterfly kernels alone
     hbm_alg = (bsk_bytes(p.n, p.N, p.l) + B * (p.n + 1) * 4 + B * (p.N + 1) * 4) // launches
     if global_shape:
         kname = f"k_wide_step<{p.N},1,1,{sched[3]},{2 if sched[5] == 4 else 1},false>"
+    elif on_matrix:
+        kname = f"k_mx_rotate<1,{sched[3]}>"
     else:
         kname = f"k_blind_rotate<{p.N},{sched[0]},1,{sched[3]}" + (",true" if sched[5] == 1 else "") + ">"
     roofline = {
@@ -268,10 +275,12 @@ def main():
         "frac": round(achieved / PEAK_LANE_OPS, 4),
         "peak_single_issue": round(SINGLE_ISSUE_LANE_OPS / 1e12, 3),
         "frac_single_issue": round(achieved / SINGLE_ISSUE_LANE_OPS, 4),
-        "mix_ceiling": round(mix / 1e12, 3),
+        "mix_ceiling": round(mix / 1e12, 3) if mix else None,
         "mix_ceiling_waves_per_simd": waves_per_simd,
-        "frac_mix_ceiling": round(achieved / mix, 4),
-        "traffic": measured_traffic(COUNTERS["global" if global_shape else "fused"]),
+        "frac_mix_ceiling": round(achieved / mix, 4) if mix else None,
+        # the op model counts the butterfly method; the matrix cores do most of it in other instructions
+        "op_model": "butterfly network",
+        "traffic": measured_traffic(COUNTERS["mx" if on_matrix else "global" if global_shape else "fused"]),
         "kernel": kname,
         "launches_per_batch": launches,
         "kernel_ms": round(per_launch * 1e3, 4),

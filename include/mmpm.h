@@ -257,12 +257,16 @@ int mm_last_timing(mm_ctx *ctx, float *blind_rotate_ms, float *keyswitch_ms);
  * workgroup slot packing, waves per component, NTT stage schedule, key-switch
  * kernel and tiling) on the device and remember the fastest for the shape (N,
  * sum of r, count).  mm_bootstrap uses the remembered schedule.  *choice
- * receives the chosen schedule index.  Untuned batches at N = 1024 that leave
- * the device mostly idle (at most two components per compute unit, or four when
- * no two-wave slots fit), or that hold more than 16 components per compute unit,
- * take the global-accumulator shape with four waves per component (each
- * component a small workgroup of its own; up to two components per compute
- * unit, with two digit groups of four waves: NTT schedule 4 below); that
+ * receives the chosen schedule index.  Untuned batches at N = 1024 run the
+ * matrix-core kernels where those apply (one prime, log2_B <= 7, l <= 4): two
+ * waves per component up to four components per compute unit (r <= 4), else one
+ * wave above one component per compute unit.  The lightest batches left, and
+ * without those kernels the ones that leave the device mostly idle (at most two
+ * components per compute unit, or four when no two-wave slots fit) or hold more
+ * than 16 components per compute unit, take the global-accumulator shape with
+ * four waves per component (each component a small workgroup of its own; up to
+ * two components per compute unit, with two digit groups of four waves: NTT
+ * schedule 4 below); that
  * shape, with its usual and with
  * twice the waves (N = 512, 1024), is a candidate for every batch the fused
  * kernel holds.  A batch on the global-accumulator path
@@ -300,7 +304,11 @@ int mm_set_schedule(mm_ctx *ctx, const int *table_ids, size_t count, int choice)
  * that leave compute units idle; 5, the global-accumulator path with two primes:
  * one workgroup per component and prime, the default up to 16 components per
  * compute unit; 6, those workgroups with two digit groups, N = 1024 and 2048,
- * the default while all of them fit one per compute unit).  Any output pointer may be NULL. */
+ * the default while all of them fit one per compute unit -- at N = 2048 with
+ * log2_B <= 15 and l <= 4 the matrix-core kernel, up to 3/2 components per compute
+ * unit, in place of 5).  Schedule 0 with workgroups of 8 waves and at most two waves
+ * per component (N = 1024), and on the global path, names the matrix-core kernels
+ * where they apply.  Any output pointer may be NULL. */
 int mm_schedule_describe(mm_ctx *ctx, const int *table_ids, size_t count, int choice, int *group_waves,
                          int *ks_cts_per_wave, int *ks_splits, int *waves_per_component, int *ks_kernel,
                          int *ntt_schedule);
