@@ -865,7 +865,7 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
         const int shape = global_shapes(c).front();
         return Sched{0, ks_after_steps(c, d, count), shape == 3 ? dev::SPLIT_WAVES : 0, shape};
     }
-    // untuned, at N = 1024 (the ring of the paper-shaped parameters, measured for
+    // untuned, at N = 1024 and without the matrix-core kernels (measured at the paper-shaped parameters for
     // r = 4 and 8 at 1024 to 16384 components; at N = 512 the fused kernel measured
     // faster up to 8192 components): the global-accumulator shape with four
     // waves per component (one component per workgroup: small workgroups, up to eight
