@@ -260,7 +260,7 @@ int mm_last_timing(mm_ctx *ctx, float *blind_rotate_ms, float *keyswitch_ms);
  * receives the chosen schedule index.  Untuned batches at N = 1024 run the
  * matrix-core kernels where those apply (one prime, log2_B <= 7, l <= 4): two
  * waves per component up to four components per compute unit (r <= 4), else one
- * wave above one component per compute unit.  The lightest batches left, and
+ * wave above two components per compute unit.  The lightest batches left, and
  * without those kernels the ones that leave the device mostly idle (at most two
  * components per compute unit, or four when no two-wave slots fit) or hold more
  * than 16 components per compute unit, take the global-accumulator shape with

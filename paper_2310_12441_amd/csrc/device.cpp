@@ -886,9 +886,11 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     // r <= 2 from the first ciphertext on, 4.2 against 6.1 for one of r = 1; with r = 4
     // one takes 6.3 either way and up to 16 components keep the digit groups; with a ternary
     // secret up to 48, whole calls of r = 4: 20 components 10.8 against 11.1, 64 11.15 either way), else one
-    // wave per component above one per compute unit (13.2 for 1600 against 16.2 with two)
+    // wave per component above two per compute unit (13.2 for 1600 against 16.2 with two; r = 8,
+    // 264 components, 11.2 against 9.5 with two digit groups, 512 11.2 against 9.9, 640 11.3 against
+    // 13.9; ternary 264 19.9 against 16.0, 512 20.0 against 16.4, 640 19.9 against 23.4)
     if (mx_two_waves(c, d, comps, two_wave ? max_r(c, ids, count) : 8u)) return Sched{8, ks_default(c, d, count), 2};
-    if (d.mx_cst && comps > cu) return Sched{8, ks_default(c, d, count), 0};
+    if (d.mx_cst && comps > 2 * cu) return Sched{8, ks_default(c, d, count), 0};
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
         (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
         return Sched{0, ks_after_steps(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};
