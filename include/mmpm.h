@@ -289,7 +289,8 @@ int mm_set_schedule(mm_ctx *ctx, const int *table_ids, size_t count, int choice)
  * key switch (0 = the i-split key switch), the number of i splits, waves per
  * ring component (1 up to N = 1024 and N / 1024 above by default; 2 at N = 512
  * and 1024 for batches that do not fill the device, r <= 4; on the global path
- * the waves of its workgroup, N / 512 up to 4096 and N / 1024 above), the key-switch
+ * the waves of its workgroup, N / 512 up to 4096 and N / 1024 above, 1 for the
+ * matrix-core step of one prime), the key-switch
  * kernel (0: i split over workgroups, per-thread sums; 1: KSK rows staged in
  * LDS, one output column per lane; 2: KSK rows staged in LDS, one ciphertext
  * per lane) and the NTT stage schedule of the blind rotation (0: every
@@ -301,14 +302,16 @@ int mm_set_schedule(mm_ctx *ctx, const int *table_ids, size_t count, int choice)
  * the stages that mix them in separate launches; 4, the global-accumulator shape
  * at N = 1024 with one prime: two groups of four waves per component, each
  * taking every other gadget digit and one part's inverse NTT, for batches
- * that leave compute units idle; 5, the global-accumulator path with two primes:
+ * that leave compute units idle (tables of r > 8 beside the matrix-core step: up to
+ * 3/2 components per compute unit); 5, the global-accumulator path with two primes:
  * one workgroup per component and prime, the default up to 16 components per
  * compute unit; 6, those workgroups with two digit groups, N = 1024 and 2048,
  * the default while all of them fit one per compute unit -- at N = 2048 with
  * log2_B <= 15 and l <= 4 the matrix-core kernel, up to 3/2 components per compute
  * unit, in place of 5).  Schedule 0 with workgroups of 8 waves and at most two waves
- * per component (N = 1024), and on the global path, names the matrix-core kernels
- * where they apply.  Any output pointer may be NULL. */
+ * per component (N = 1024), and on the global path with one wave per component (N = 1024)
+ * or two primes (N = 2048), names the matrix-core kernels where they apply.  Any output
+ * pointer may be NULL. */
 int mm_schedule_describe(mm_ctx *ctx, const int *table_ids, size_t count, int choice, int *group_waves,
                          int *ks_cts_per_wave, int *ks_splits, int *waves_per_component, int *ks_kernel,
                          int *ntt_schedule);

@@ -716,9 +716,10 @@ int primes_of(const mm_ctx &c) { return c.wide ? 2 : 1; }
 // CMux step (NTT schedule 0; rings up to 16384), or the ring split into
 // sub-rings of 8192 (schedule 3; one prime, rings of 16384 and more); with two
 // primes also one workgroup per component and prime (5), of two digit groups
-// (6, N = 1024 and 2048).
-static std::vector<int> global_shapes(const mm_ctx &c)
+// (6, N = 1024 and 2048); beside the matrix-core step of one prime two digit groups (4).
+static std::vector<int> global_shapes(const mm_ctx &c, const Device &d)
 {
+    if (d.mx_cst && !c.wide) return {0, 4};
     if (c.wide) {
         std::vector<int> v{0};
         if (dev::wide_supports_ps(c.p.N, 2)) v.push_back(5);
@@ -728,6 +729,12 @@ static std::vector<int> global_shapes(const mm_ctx &c)
     if (!dev::split_supports_n(c.p.N)) return {0};
     if (c.p.N > 16384) return {3};
     return {0, 3};
+}
+
+// Waves per component of such a shape (0: the usual).
+static int global_wpp(const mm_ctx &c, int shape)
+{
+    return shape == 3 ? dev::SPLIT_WAVES : shape == 4 ? light_global_wpp(c) : 0;
 }
 
 // The global-accumulator shape as a schedule of batches the fused kernel holds
@@ -815,8 +822,8 @@ static std::vector<Sched> candidates(const mm_ctx &c, const Device &d, const int
         for (uint32_t P : {2u, 3u, 4u, 6u}) add(KsSched{KS_LANES, P});
     if (count < 256) ks.push_back(KsSched{0, ks_splits(c, d, count)});
     if (use_global(c, ids, count)) {
-        for (int shape : global_shapes(c))
-            for (auto &k : ks) out.push_back(Sched{0, k, shape == 3 ? dev::SPLIT_WAVES : 0, shape});
+        for (int shape : global_shapes(c, d))
+            for (auto &k : ks) out.push_back(Sched{0, k, global_wpp(c, shape), shape});
         return out;
     }
     for (int gw : {8, 4}) {
@@ -862,8 +869,12 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
         const uint64_t comps = sum_r(c, ids, count);
         if (prime_split(c, d, comps))
             return Sched{0, ks_after_steps(c, d, count), 0, prime_split_dg(c, d, comps) == 2 ? 6 : 5};
-        const int shape = global_shapes(c).front();
-        return Sched{0, ks_after_steps(c, d, count), shape == 3 ? dev::SPLIT_WAVES : 0, shape};
+        // one prime on the matrix cores: two digit groups stay the faster shape up to 3/2 components
+        // per compute unit (630 steps, ms: 16 components 6.3 against 10.2, 256 7.8 against 10.8; 512
+        // 12.2 against 11.3)
+        const bool light = d.mx_cst && !c.wide && 2 * comps <= 3ull * (uint64_t)d.num_cu;
+        const int shape = light ? 4 : global_shapes(c, d).front();
+        return Sched{0, ks_after_steps(c, d, count), global_wpp(c, shape), shape};
     }
     // untuned, at N = 1024 and without the matrix-core kernels (measured at the paper-shaped parameters for
     // r = 4 and 8 at 1024 to 16384 components; at N = 512 the fused kernel measured
@@ -1170,14 +1181,16 @@ static void blind_rotate_wide(mm_ctx &c, Device &d, const int *ids, const uint32
     uint32_t *acc0 = (uint32_t *)ws(d, WS_ACC, words * 4);
     uint32_t *acc1 = (uint32_t *)ws(d, WS_ACC2, words * 4);
     dev::WideArgs A = wide_args(c, d);
-    if (schedule_for(c, d, ids, count).ntt == 3) split_buffers(c, d, A, tasks.size());
+    const Sched S = schedule_for(c, d, ids, count);
+    if (S.ntt == 3) split_buffers(c, d, A, tasks.size());
     dev::WideTask *dt;
     uint64_t *doff;
     upload_wide(d, tasks, offs, &dt, &doff, st);
     A.tasks = dt;
     A.ct_in = d_in;
     const uint32_t nt = (uint32_t)tasks.size();
-    A.acc_rd = enqueue_wide_rotation(c, A, acc0, acc1, nt, steps, st);
+    // one prime: the schedule's shape; two: one workgroup per component whatever the count
+    A.acc_rd = enqueue_wide_rotation(c, A, acc0, acc1, nt, steps, st, S.ntt == 4 ? S.wpp : 0, S.ntt == 4 ? 2 : 1);
     if (c.wide) dev::launch_wide_export(c.p.N, A, nt, d_acc, st);
     else HIPC(hipMemcpyAsync(d_acc, A.acc_rd, words * 4, hipMemcpyDeviceToDevice, st));  // already [comp][part][N]
     HIPC(hipGetLastError());
@@ -1420,7 +1433,11 @@ void describe_schedule(mm_ctx &c, const int *ids, size_t count, int choice, int 
     if (ks_kernel) *ks_kernel = S.ks.cpw == KS_LANES ? 2 : (S.ks.cpw > 0 ? 1 : 0);
     if (ntt) *ntt = S.ntt;
     if (P) *P = (int)S.ks.P;
-    if (wpp) *wpp = S.wpp ? S.wpp : (S.gw == 0 ? dev::wide_waves_per_poly(c.p.N) : dev::waves_per_poly(c.p.N));
+    // the matrix-core step of one prime: one wave per component
+    const bool mx_step = d.mx_cst && !c.wide && S.gw == 0 && S.ntt == 0;
+    if (wpp)
+        *wpp = S.wpp ? S.wpp
+                     : S.gw == 0 && !mx_step ? dev::wide_waves_per_poly(c.p.N) : dev::waves_per_poly(c.p.N);
 }
 
 // The global-accumulator path: time each blind-rotation shape (at N = 16384 one
@@ -1438,7 +1455,7 @@ static int autotune_global(mm_ctx &c, Device &d, const int *ids, const uint32_t 
     int best_shape = cand[0].ntt;
     size_t best_k = 0;
     try {
-        const std::vector<int> shapes = global_shapes(c);
+        const std::vector<int> shapes = global_shapes(c, d);
         float best = 1e30f;
         for (int shape : shapes) {
             size_t k0 = 0;

@@ -169,6 +169,7 @@ void launch_wide_init(uint32_t N, int npr, const WideArgs &A, uint32_t num_tasks
 // wpp: waves per component workgroup (0: wide_waves_per_poly(N)); with one prime
 // also twice that at N = 512 and 1024 (wide_supports_wpp).
 // dg = 2 (N = 1024, wpp = 4, one prime): two digit groups of wpp waves per component.
+// wpp = 0, dg = 1 is the matrix-core step where it applies, as are two digit groups with ps at N = 2048.
 // ps (two primes): one workgroup per component and prime (dg = 2 too: N = 1024, 2048).
 void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st,
                       int wpp = 0, int dg = 1, bool ps = false);

@@ -622,16 +622,9 @@ static void ps_launch(uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipS
 void launch_wide_step(uint32_t N, int npr, uint32_t keys, const WideArgs &A, uint32_t num_tasks, hipStream_t st,
                       int wpp, int dg, bool ps)
 {
-    if (A.mx.cst && dg == 1 && !ps) {
-        // the matrix cores; at one prime and up to 3/2 components per compute unit the two digit
-        // groups below stay the faster shape (630 steps, ms: 16 components 6.3 against 10.2,
-        // 256 7.8 against 10.8; 512 12.2 against 11.3)
-        if (npr == 2 || 2 * num_tasks > 3 * A.mx.num_cu) {
-            launch_mx_step(N, npr, keys, A, num_tasks, st);
-            return;
-        }
-        dg = 2;
-        wpp = 4;
+    if (A.mx.cst && wpp == 0 && dg == 1 && !ps) {
+        launch_mx_step(N, npr, keys, A, num_tasks, st);
+        return;
     }
     if (ps && npr == 2) {
         if (dg == 2 && N == 1024) ps_launch<1024, 2, 2>(keys, A, num_tasks, st);
