@@ -781,11 +781,9 @@ int light_global_dg(const mm_ctx &c, const Device &d, uint64_t comps)
     return w2 && dev::wide_supports_dg(c.p.N, primes_of(c), w2) && comps <= 2ull * (uint64_t)d.num_cu ? 2 : 1;
 }
 
-// The matrix-core kernel with two waves per component: see schedule_for.
-bool mx_two_waves(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r)
+LightWork light_work(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r)
 {
-    return d.mx_cst && !c.wide && max_r <= 4 && comps <= 4ull * (uint64_t)d.num_cu &&
-           (max_r <= 2 || comps > (c.keys == 2 ? 48u : 16u));
+    return LightWork{comps, max_r, c.keys, (uint64_t)d.num_cu, d.mx_cst && !c.wide};
 }
 
 // Two waves per component (N = 512, 1024, r <= 4): for batches that do not
@@ -876,35 +874,24 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
         const int shape = light ? 4 : global_shapes(c, d).front();
         return Sched{0, ks_after_steps(c, d, count), global_wpp(c, shape), shape};
     }
-    // untuned, at N = 1024 and without the matrix-core kernels (measured at the paper-shaped parameters for
-    // r = 4 and 8 at 1024 to 16384 components; at N = 512 the fused kernel measured
-    // faster up to 8192 components): the global-accumulator shape with four
-    // waves per component (one component per workgroup: small workgroups, up to eight
-    // waves per SIMD) where it measured fastest -- batches that leave the device mostly
-    // idle (at most two components per compute unit, or four where the components
-    // cannot take two-wave slots: one ciphertext 7.4 ms instead of 14.2 ms, or 25.9 ms
-    // at r = 8) and batches of more than 16 components per compute unit (188.8 against
-    // 203.8 ms for 16,384); in between the fused kernel (two-wave slots up to four
-    // components per compute unit, 14.6 against 16.5 ms at 1024; one wave per component
-    // up to 16 per compute unit, 25.6 against 27.4 ms at 2048).  Up to two components
-    // per compute unit, two digit groups per component (6.5 against 7.4 ms for one
-    // ciphertext, 12.2 against 12.7 ms for 512 components; 20.3 against 18.2 ms at 1024)
+    // untuned, at N = 1024 (light_rules.hpp): light work by two waves per component on the
+    // matrix cores or by one launch per step with four waves per component (up to two components
+    // per compute unit two digit groups: 6.5 against 7.4 ms for one ciphertext, 12.2 against 12.7 ms
+    // for 512 components; 20.3 against 18.2 ms at 1024), more by one wave per component on the matrix
+    // cores (13.2 ms for 1600 against 16.2 with two).  Without the matrix-core kernels (measured
+    // at the paper-shaped parameters for r = 4 and 8 at 1024 to 16384 components; at N = 512 the
+    // fused kernel measured faster up to 8192 components) one launch per step also above 16 components
+    // per compute unit (188.8 against 203.8 ms for 16,384); in between the fused kernel (two-wave
+    // slots up to four components per compute unit, 14.6 against 16.5 ms at 1024; one wave per
+    // component up to 16 per compute unit, 25.6 against 27.4 ms at 2048)
     const uint64_t comps = sum_r(c, ids, count), cu = (uint64_t)d.num_cu;
     const bool two_wave = wide_slots_ok(c, ids, count);
-    // where the matrix-core kernel applies (630 steps, ms): two waves per component up to four
-    // components per compute unit where every ciphertext fits such slots (148 components 7.0,
-    // 400 7.9, 1024 9.2; two digit groups 7.5, 11.0, 19.1; one wave 8.0, 8.8, 9.6; with
-    // r <= 2 from the first ciphertext on, 4.2 against 6.1 for one of r = 1; with r = 4
-    // one takes 6.3 either way and up to 16 components keep the digit groups; with a ternary
-    // secret up to 48, whole calls of r = 4: 20 components 10.8 against 11.1, 64 11.15 either way), else one
-    // wave per component above two per compute unit (13.2 for 1600 against 16.2 with two; r = 8,
-    // 264 components, 11.2 against 9.5 with two digit groups, 512 11.2 against 9.9, 640 11.3 against
-    // 13.9; ternary 264 19.9 against 16.0, 512 20.0 against 16.4, 640 19.9 against 23.4)
-    if (mx_two_waves(c, d, comps, two_wave ? max_r(c, ids, count) : 8u)) return Sched{8, ks_default(c, d, count), 2};
-    if (d.mx_cst && comps > 2 * cu) return Sched{8, ks_default(c, d, count), 0};
+    const LightWork work = light_work(c, d, comps, max_r(c, ids, count));
+    if (two_mx_waves(work)) return Sched{8, ks_default(c, d, count), 2};
     if (global_ok(c) && c.p.N == 1024 && light_global_wpp(c) &&
-        (comps <= 2 * cu || (!two_wave && comps <= 4 * cu) || comps > 16 * cu))
+        (steps_by_launch(work) || (!work.mx && comps > 16 * cu)))
         return Sched{0, ks_after_steps(c, d, count), light_global_wpp(c), light_global_dg(c, d, comps) == 2 ? 4 : 0};
+    if (work.mx) return Sched{8, ks_default(c, d, count), 0};
     if (comps <= 4 * cu && two_wave) return Sched{8, ks_default(c, d, count), 2};
     // rings of several waves per component: groups of four waves (two workgroups per compute
     // unit, each its own barriers) where the last round of eight-wave groups would be at most

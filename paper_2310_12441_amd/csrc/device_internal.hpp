@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "light_rules.hpp"
 #include "mmpm_internal.hpp"
 
 namespace mm {
@@ -126,7 +127,7 @@ dev::WideArgs wide_args(const mm_ctx &c, const Device &d);
 int primes_of(const mm_ctx &c);
 int light_global_wpp(const mm_ctx &c);  // waves per component of light global-path work (0: the usual)
 int light_global_dg(const mm_ctx &c, const Device &d, uint64_t comps);  // digit groups of such work
-bool mx_two_waves(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r);  // matrix cores, light work
+LightWork light_work(const mm_ctx &c, const Device &d, uint64_t comps, uint32_t max_r);
 bool prime_split(const mm_ctx &c, const Device &d, uint64_t comps);     // one workgroup per prime
 int prime_split_dg(const mm_ctx &c, const Device &d, uint64_t comps);   // digit groups of those
 

@@ -437,18 +437,14 @@ void Server::launch(Part &p)
     }
     bool glob = global;
     if (switchable) {
-        // the rule of the batched path's default schedule: at most two components per
-        // compute unit, or four where the components cannot take two-wave slots; on the
-        // matrix cores what its two-wave slots do not take, up to one per compute unit
+        // the batched path's rule for light work
         uint64_t comps = 0;
         uint32_t max_r = 1;
         for (auto &a : p.active) {
             comps += c->tables[a.table].r;
             max_r = std::max(max_r, c->tables[a.table].r);
         }
-        const uint64_t cu = (uint64_t)d.num_cu;
-        if (d.mx_cst) glob = !mx_two_waves(*c, d, comps, max_r) && comps <= cu;
-        else glob = comps <= 2 * cu || (max_r > 4 && comps <= 4 * cu);
+        glob = steps_by_launch(light_work(*c, d, comps, max_r));
     }
     if (glob) {
         launch_global(p, fresh);
