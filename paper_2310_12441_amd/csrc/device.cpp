@@ -656,7 +656,7 @@ KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 // next call's steps, each a launch that starts on the bootstrapping key in memory, run longer
 // for it (call of 1 ciphertext of r = 4 6.37 ms against 6.60, 16 of r = 8 6.65 against 6.80, 24
 // 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).
-static KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count)
+KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count)
 {
     return count <= 16 ? KsSched{0, ks_splits(c, d, count)} : ks_default(c, d, count);
 }

@@ -114,6 +114,7 @@ std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uin
 dev::MxArgs mx_args(const mm_ctx &c, const Device &d);
 uint32_t spread_cap(const Device &d, uint64_t comps, uint32_t gw, uint32_t wpp);
 KsSched ks_default(const mm_ctx &c, const Device &d, size_t count);
+KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count);  // behind one launch per step
 size_t ks_part_words(const mm_ctx &c, const KsSched &k, size_t count);
 dev::BrArgs br_args(const mm_ctx &c, const Device &d);
 uint32_t ks_splits(const mm_ctx &c, const Device &d, size_t count);

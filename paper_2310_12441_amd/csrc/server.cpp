@@ -599,7 +599,7 @@ void Server::launch_global(Part &p, const std::vector<Active> &fresh)
         }
         SRV_HIP(hipMemcpyAsync(p.woff.d, p.woff.h, F * 8, hipMemcpyHostToDevice, p.st));
         SRV_HIP(hipMemcpyAsync(p.qout.d, p.qout.h, F * 4, hipMemcpyHostToDevice, p.st));
-        const KsSched ks = ks_default(*c, d, F);
+        const KsSched ks = ks_after_steps(*c, d, F);
         const size_t need = ks_part_words(*c, ks, F);
         if (p.part_cap < need || p.ext_cap < F) {
             SRV_HIP(hipStreamSynchronize(p.st));
