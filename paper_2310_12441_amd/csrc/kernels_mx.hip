@@ -29,6 +29,7 @@
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "rotation_common.hpp"
+#include "wrap64.hpp"
 
 namespace mm {
 namespace dev {
@@ -56,7 +57,7 @@ __device__ __forceinline__ void redc4(int64_t (&t)[4], const ModS &m, int32_t (&
     for (int s = 0; s < 4; s++) q[s] = (int32_t)((uint32_t)t[s] * m.qn);
     __asm__("" : "+v"(q[0]), "+v"(q[1]), "+v"(q[2]), "+v"(q[3]));
 #pragma unroll
-    for (int s = 0; s < 4; s++) o[s] = (int32_t)((t[s] + (int64_t)q[s] * m.Q) >> 32);
+    for (int s = 0; s < 4; s++) o[s] = (int32_t)(mad_wrap(q[s], m.Q, t[s]) >> 32);
 }
 
 __device__ __forceinline__ v16i mfma(v4i a, v4i b, v16i c) { return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0); }
@@ -137,9 +138,9 @@ __device__ __forceinline__ void mx_twist(int t, const int32_t (&lo)[16], const i
     if (!(t & 1)) {
         const v4i w = tw[2 * q * pitch], w16 = tw[(2 * q + 1) * pitch];
 #pragma unroll
-        for (int s = 0; s < 4; s++) s4[s] = (int64_t)hi[4 * q + s] * w16[s] + X.bal64;
+        for (int s = 0; s < 4; s++) s4[s] = mad_wrap(hi[4 * q + s], w16[s], X.bal64);
 #pragma unroll
-        for (int s = 0; s < 4; s++) s4[s] += (int64_t)lo[4 * q + s] * w[s];
+        for (int s = 0; s < 4; s++) s4[s] = mad_wrap(lo[4 * q + s], w[s], s4[s]);
     } else {
         int32_t o[4];
         redc4(s4, m, o);
@@ -274,7 +275,7 @@ __device__ __forceinline__ void mx_cut(int q, const int64_t (&acc)[16], const Mx
 #pragma unroll
     for (int s = 0; s < 4; s++) {
         const uint64_t low = (uint32_t)acc[4 * q + s] | ((uint64_t)BAL << 32);
-        s4[s] = (int64_t)(int32_t)(acc[4 * q + s] >> 32) * X.two32 + (int64_t)low;
+        s4[s] = mad_wrap((int32_t)(acc[4 * q + s] >> 32), X.two32, (int64_t)low);
     }
     redc4(s4, m, o);
 #pragma unroll
