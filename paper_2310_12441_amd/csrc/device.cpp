@@ -354,22 +354,6 @@ void device_init(mm_ctx &c, int id)
     }
     upload(&d->bsk, kb.data(), kb.size());
     upload(&d->bsk_corr, corr.data(), corr.size());
-    const std::vector<uint32_t> cst = mx_applies(c) ? mx_tables(c) : std::vector<uint32_t>{};
-    if (!cst.empty()) {
-        upload(&d->mx_cst, cst.data(), cst.size());
-        if (hipMalloc((void **)&d->mx_bsk, kb.size() * 4) != hipSuccess) {
-            d->mx_bsk = nullptr;
-            throw Error(MM_ENOMEM, "device key allocation failed");
-        }
-        const uint32_t primes = c.wide ? 2 : 1, block = 2 * p.l * 2;
-        for (uint32_t pr = 0; pr < primes; pr++) {
-            const uint32_t Qp = pr ? p.Q2 : Q;
-            dev::launch_mx_keys(N, d->bsk, d->mx_bsk, kb.size() / N / primes, Qp, pr ? d->qn2 : d->qn,
-                                to_mont(to_mont(1, Qp), Qp), block, primes, pr, nullptr);
-        }
-        HIPC(hipGetLastError());
-        HIPC(hipDeviceSynchronize());
-    }
     {
         // the key-switching key in column tiles, [i][tile][l_ks B_ks][64], a few
         // coordinates at a time through a host buffer
@@ -400,6 +384,29 @@ void device_init(mm_ctx &c, int id)
     HIPC(dev::init_kernel_attributes());
     HIPC(dev::noalloc_scratch_init(id, &d->scratch));
     HIPC(hipStreamCreateWithFlags(&d->own, hipStreamNonBlocking));
+    // the matrix-core kernels' own copy of the bootstrapping key, last and only where the device has
+    // room for it: without it the other kernels run
+    const std::vector<uint32_t> cst = mx_applies(c) ? mx_tables(c) : std::vector<uint32_t>{};
+    if (!cst.empty()) {
+        uint32_t *block_cst = nullptr;
+        if (hipMalloc((void **)&block_cst, cst.size() * 4) == hipSuccess &&
+            hipMalloc((void **)&d->mx_bsk, kb.size() * 4) == hipSuccess) {
+            d->mx_cst = block_cst;
+            HIPC(hipMemcpy(d->mx_cst, cst.data(), cst.size() * 4, hipMemcpyHostToDevice));
+            const uint32_t primes = c.wide ? 2 : 1, block = 2 * p.l * 2;
+            for (uint32_t pr = 0; pr < primes; pr++) {
+                const uint32_t Qp = pr ? p.Q2 : Q;
+                dev::launch_mx_keys(N, d->bsk, d->mx_bsk, kb.size() / N / primes, Qp, pr ? d->qn2 : d->qn,
+                                    to_mont(to_mont(1, Qp), Qp), block, primes, pr, nullptr);
+            }
+            HIPC(hipGetLastError());
+            HIPC(hipDeviceSynchronize());
+        } else {
+            d->mx_bsk = nullptr;
+            if (block_cst) HIPC(hipFree(block_cst));
+            (void)hipGetLastError();
+        }
+    }
     c.dev = std::move(d);
 }
 
