@@ -29,3 +29,14 @@ def test_bursts_at_1024(ternary):
     for count in (1, 16, 17, 64, 70):
         _served(s, [8] * count, np.zeros(count, np.int64))
     s.ctx.close()
+
+
+@pytest.mark.parametrize("ternary", [False, True])
+def test_two_primes_at_2048(ternary):
+    """Few components (one workgroup per component and prime) and more than 3/2 per compute unit (two
+    components per workgroup), arriving over several ticks, so that a workgroup's two components may stand
+    at different steps."""
+    s = Setup(Params(n=7, N=2048, log2_B=15, l=4, Q2=Q2_DEFAULT, ternary=ternary), 3210 + ternary)
+    _served(s, [2, 1, 5], np.zeros(3, np.int64))
+    _served(s, [3] * 320, np.arange(320) // 4 * 20_000)
+    s.ctx.close()
