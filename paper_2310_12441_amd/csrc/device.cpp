@@ -145,14 +145,13 @@ static bool mx_applies(const mm_ctx &c)
     return true;
 }
 
-// The constant block of two primes, N = 2048 (MxWide in kernels_mx.hip).  Empty where a limb's
-// sum could leave 32 bits once joined to the next one (128 times a row's bytes, times 257): the
-// kernels then do not apply.
+// The constant block of two primes, N = 2048 (MxWide in kernels_mx.hip).  A limb's sum has at most
+// 256 terms (64 rows of four bytes, the last stage), and joined to the next one stays in 32 bits.
 static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
 {
     const uint32_t N = c.p.N, T1 = 2, D = 2, NB = T1 * D;
     std::vector<uint32_t> out(dev::MX_WIDE_CONST_WORDS, 0);
-    bool fits = true;
+    static_assert(32ull * T1 * 4 * 128 * 128 * 257 < (1ull << 31), "joined limb sums");
     for (uint32_t pr = 0; pr < D; pr++) {
         const NttTables &T = pr ? c.ntt2 : c.ntt;
         const uint32_t Q = T.Q, nl = pr ? 3 : 4, ia = 8 * T1;
@@ -164,14 +163,12 @@ static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
         auto at = [&](int64_t e) { return pw[(size_t)(((e % (2 * (int64_t)N)) + 2 * N) % (2 * N))]; };
         const size_t lds = (size_t)pr * ops(4) * 256;
         const size_t mem = ((size_t)ops(4) + ops(3) + pr * (ia + 16 * T1 * T1)) * 256;
-        std::vector<uint64_t> sums;  // per limb of one output: the sum of the constant's bytes
         // the four limbs of w 2^(8 m), byte b of a lane of operands at + 256 j
         auto put = [&](size_t at_op, uint32_t lane, uint32_t b, uint32_t w, uint32_t m) {
             const int32_t v = centred(mulmod(w, (uint32_t)((1ull << (8 * m)) % Q), Q), Q);
             for (uint32_t j = 0; j < nl; j++) {
                 const uint32_t byte = balanced_byte(v, j);
                 out[at_op + ((size_t)j * 64 + lane) * 4 + b / 4] |= byte << (8 * (b % 4));
-                sums[j] += (uint64_t)std::abs((int)(int8_t)byte);
             }
         };
         auto word = [&](size_t at_op, uint32_t lane, uint32_t s, uint32_t w) {  // w and 2^16 w, Montgomery form
@@ -179,11 +176,6 @@ static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
             out[at_op + lane * 4 + s] = (uint32_t)centred(f, Q);
             out[at_op + 256 + lane * 4 + s] = (uint32_t)centred(mulmod(f, 65536 % Q, Q), Q);
         };
-        auto bounded = [&] {
-            for (uint64_t v : sums) fits = fits && v * 128 * 257 < (1ull << 31);
-            sums.assign(4, 0);
-        };
-        sums.assign(4, 0);
         for (uint32_t col = 0; col < 32; col++) {
             for (uint32_t tile = 0; tile < T1; tile++) {
                 const int64_t k1 = 32 * tile + col;
@@ -193,7 +185,6 @@ static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
                         const uint32_t per = 32 / D, b = i1 / per, h = i1 % per / (16 / D), e = i1 % (16 / D);
                         put(lds + (tile * NB + b) * nl * 256, col + 32 * h, D * e + m, at(32 * (int64_t)i1 * (2 * k1 + 1)), m);
                     }
-                bounded();
                 // last stage: values k1' (tile ti, row) for output i1 = k1
                 for (uint32_t ti = 0; ti < T1; ti++)
                     for (uint32_t row = 0; row < 32; row++)
@@ -202,7 +193,6 @@ static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
                             put(mem + (ia + ((tile * T1 + ti) * 4 + row / 8) * nl) * 256, col + 32 * (row / 4 % 2),
                                 4 * (row % 4) + m, at(-32 * k1 * (2 * kk + 1)), m);
                         }
-                bounded();
                 for (int64_t row = 0; row < 32; row++) {
                     const uint32_t q = (uint32_t)row / 8, lane = col + 32 * ((uint32_t)row / 4 % 2), s = (uint32_t)row % 4;
                     // value (i2 = row, k1) forward; (k1' = 32 tile + row, i2 = col) inverse
@@ -215,10 +205,8 @@ static std::vector<uint32_t> mx_wide_tables(const mm_ctx &c)
                 for (uint32_t m = 0; m < 4; m++)
                     put(lds + (fb + (uint32_t)row / 8 * nl) * 256, col + 32 * ((uint32_t)row / 4 % 2),
                         4 * ((uint32_t)row % 4) + m, at((int64_t)(N / 16) * row * col), m);
-            bounded();
         }
     }
-    if (!fits) out.clear();
     return out;
 }
 
@@ -386,8 +374,8 @@ void device_init(mm_ctx &c, int id)
     HIPC(hipStreamCreateWithFlags(&d->own, hipStreamNonBlocking));
     // the matrix-core kernels' own copy of the bootstrapping key, last and only where the device has
     // room for it: without it the other kernels run
-    const std::vector<uint32_t> cst = mx_applies(c) ? mx_tables(c) : std::vector<uint32_t>{};
-    if (!cst.empty()) {
+    if (mx_applies(c)) {
+        const std::vector<uint32_t> cst = mx_tables(c);
         uint32_t *block_cst = nullptr;
         if (hipMalloc((void **)&block_cst, cst.size() * 4) == hipSuccess &&
             hipMalloc((void **)&d->mx_bsk, kb.size() * 4) == hipSuccess) {
