@@ -37,16 +37,21 @@ SINGLE_ISSUE_LANE_OPS = 256 * 64 * 2.4e9
 # instruction mix can reach (4.817e12 butterflies/s at 2 waves per SIMD, 4.957e12
 # at 5).
 MIX_CEILING_LANE_OPS = {2: 38.5e12, 5: 39.7e12}
+# Wave instructions: four clocks of a SIMD for a vector one, 32 of its matrix unit for a
+# v_mfma_i32_32x32x32_i8 (65,536 operations: 5.0e15/s, the dense int8 rate).
+PEAK_WAVE_INSTS = 1024 * 2.4e9 / 4
+PEAK_MATRIX_INSTS = 1024 * 2.4e9 / 32
 PEAK_HBM = 8.0e12
 KERNEL_SOURCES = ("paper_2310_12441_amd/csrc/kernels.hip", "paper_2310_12441_amd/csrc/kernels_wide.hip",
                   "paper_2310_12441_amd/csrc/kernels_mx.hip", "paper_2310_12441_amd/csrc/rotation_common.hpp",
-                  "paper_2310_12441_amd/csrc/device_common.hpp")
-# counter summaries of the blind-rotation kernels the schedule can pick for the
+                  "paper_2310_12441_amd/csrc/wrap64.hpp", "paper_2310_12441_amd/csrc/device_common.hpp")
+# counter summaries of blind-rotation kernels the schedule can pick for the
 # paper-shaped batch: the fused persistent kernels (matrix cores, butterflies), and the
-# global-accumulator kernel with four waves per component (one launch per CMux step)
+# butterfly step of four waves per component (one launch per CMux step)
 COUNTERS = {"mx": os.path.join(ROOT, "profiles", "k_mx_rotate_paper_shaped_4096_counters.txt"),
             "fused": os.path.join(ROOT, "profiles", "k_blind_rotate_paper_shaped_4096_counters.txt"),
-            "global": os.path.join(ROOT, "profiles", "k_wide_step_paper_shaped_4096_counters.txt")}
+            "global": os.path.join(ROOT, "profiles", "k_wide_step_paper_shaped_4096_counters.txt"),
+            "none": ""}  # no counters kept
 
 
 def ops_per_bootstrap(n, N, l, r):
@@ -67,6 +72,13 @@ def ops_per_bootstrap(n, N, l, r):
     bfly = (N // 2) * logN
     per_comp = 2 * l * bfly * 11 + 2 * bfly * 10 + 2 * N * l * 10
     return n * r * per_comp
+
+
+def matrix_insts_per_bootstrap(n, l, r, keys=1):
+    """Matrix instructions of one blind rotation at N = 1024: per step, component and key 2l digit
+    polynomials of 4 + 16 (the first stage contracts bytes, the second the residues' bytes),
+    and two inverse transforms of 16 + 16."""
+    return n * r * (keys * 2 * l * (4 + 16) + 2 * (16 + 16))
 
 
 # The paper's own times for the same workload (identity f by two bootstraps, n = 2^9,
@@ -101,9 +113,9 @@ def source_hash():
     return h.hexdigest()[:16]
 
 
-def measured_traffic(path):
-    """HBM bytes per launch of a blind-rotation kernel from its committed counter
-    summary, or None when it is missing or the kernel sources changed since."""
+def measured(path, key):
+    """A per-launch figure of a blind-rotation kernel from its committed counter summary, or None
+    when it is missing or the kernel sources changed since."""
     if not os.path.exists(path):
         return None
     kv = {}
@@ -114,7 +126,7 @@ def measured_traffic(path):
     if kv.get("kernel_source_sha256_16") != source_hash():
         return None
     try:
-        return int(kv["hbm_bytes_per_launch"])
+        return int(kv[key])
     except (KeyError, ValueError):
         return None
 
@@ -245,51 +257,70 @@ def main():
         plain_out = torch.cat(plain_outs).cpu().numpy().view(np.uint32)
         plain_same = bool(np.array_equal(plain_out, batched_out[:P]))
 
-    # ---- roofline of the blind-rotation kernel the schedule picked: the fused
-    # persistent kernel (one launch per batch) or the global-accumulator kernel (one
-    # launch per CMux step, plus an initialisation and an extraction launch inside the
-    # same HIP-event bracket, so the per-launch time below is slightly conservative)
+    # ---- roofline of the blind-rotation kernel the schedule picked: a fused persistent
+    # kernel (one launch per batch) or one launch per CMux step (plus an initialisation
+    # and an extraction launch inside the same HIP-event bracket, so the per-launch
+    # time below is slightly conservative)
     br_avg = float(np.mean(br_ms)) * 1e-3
-    global_shape = sched[0] == 0
-    launches = p.n if global_shape else 1
+    per_step = sched[0] == 0
+    launches = p.n if per_step else 1
     per_launch = br_avg / launches
-    ops = ops_per_bootstrap(p.n, p.N, p.l, r) * B // launches
-    achieved = ops / per_launch
-    # eight-wave groups of the lockstep schedule run on the matrix cores where those kernels apply
-    on_matrix = (not global_shape and sched[0] == 8 and sched[5] == 0 and p.N == 1024 and p.log2_B <= 7 and p.l <= 4
-                 and not p.Q2)
-    waves_per_simd = 5 if global_shape else 2  # VGPR-bound occupancy of each kernel (94 and 256 VGPRs)
-    mix = None if on_matrix else MIX_CEILING_LANE_OPS[waves_per_simd]  # a ceiling of the butterfly kernels alone
+    # where the matrix-core kernels apply their step is a schedule of its own, one wave per component
+    has_matrix = p.N == 1024 and any(d[0] == 0 and d[3] == 1 for d in
+                                     (ctx.schedule_describe(ids, k) for k in range(ctx.schedule_count(ids))))
+    on_matrix = has_matrix and sched[5] == 0 and (sched[3] == 1 if per_step else sched[0] == 8 and sched[3] <= 2)
     hbm_alg = (bsk_bytes(p.n, p.N, p.l) + B * (p.n + 1) * 4 + B * (p.N + 1) * 4) // launches
-    if global_shape:
+    if on_matrix:
+        kname = "k_mx_step<1>" if per_step else f"k_mx_rotate<1,{sched[3]}>"
+    elif per_step:
         kname = f"k_wide_step<{p.N},1,1,{sched[3]},{2 if sched[5] == 4 else 1},false>"
-    elif on_matrix:
-        kname = f"k_mx_rotate<1,{sched[3]}>"
     else:
         kname = f"k_blind_rotate<{p.N},{sched[0]},1,{sched[3]}" + (",true" if sched[5] == 1 else "") + ">"
-    roofline = {
-        "bound": "alu",
-        "achieved": round(achieved / 1e12, 3),
-        "peak": round(PEAK_LANE_OPS / 1e12, 3),
-        "unit": "TOP/s",
-        "frac": round(achieved / PEAK_LANE_OPS, 4),
-        "peak_single_issue": round(SINGLE_ISSUE_LANE_OPS / 1e12, 3),
-        "frac_single_issue": round(achieved / SINGLE_ISSUE_LANE_OPS, 4),
-        "mix_ceiling": round(mix / 1e12, 3) if mix else None,
-        "mix_ceiling_waves_per_simd": waves_per_simd,
-        "frac_mix_ceiling": round(achieved / mix, 4) if mix else None,
-        # the op model counts the butterfly method; the matrix cores do most of it in other instructions
-        "op_model": "butterfly network",
-        "traffic": measured_traffic(COUNTERS["mx" if on_matrix else "global" if global_shape else "fused"]),
+    counters = COUNTERS["mx" if kname == "k_mx_rotate<1,1>" else "global" if kname == "k_wide_step<1024,1,1,4,1,false>"
+                        else "fused" if kname.startswith("k_blind_rotate<1024,8,1,1") else "none"]
+    roofline = {"bound": "alu"}
+    if on_matrix:
+        # vector issue (counted instructions, the matrix ones among them, over the time measured here)
+        # and the matrix units (instructions that the transforms need)
+        insts = measured(counters, "vector_instructions_per_launch")
+        matrix = matrix_insts_per_bootstrap(p.n, p.l, r) * B // launches
+        roofline.update({
+            "achieved": round(insts / per_launch / 1e9, 1) if insts else None,
+            "peak": round(PEAK_WAVE_INSTS / 1e9, 1),
+            "unit": "G wave instructions/s",
+            "frac": round(insts / per_launch / PEAK_WAVE_INSTS, 4) if insts else None,
+            "matrix_tops": round(matrix / per_launch * 65536 / 1e12, 1),
+            "matrix_peak_tops": round(PEAK_MATRIX_INSTS * 65536 / 1e12, 1),
+            "matrix_frac": round(matrix / per_launch / PEAK_MATRIX_INSTS, 4),
+            "matrix_instructions_per_launch": matrix,
+        })
+    else:
+        ops = ops_per_bootstrap(p.n, p.N, p.l, r) * B // launches
+        achieved = ops / per_launch
+        waves_per_simd = 5 if per_step else 2  # VGPR-bound occupancy of each kernel (94 and 256 VGPRs)
+        mix = MIX_CEILING_LANE_OPS[waves_per_simd]
+        roofline.update({
+            "achieved": round(achieved / 1e12, 3),
+            "peak": round(PEAK_LANE_OPS / 1e12, 3),
+            "unit": "TOP/s",
+            "frac": round(achieved / PEAK_LANE_OPS, 4),
+            "peak_single_issue": round(SINGLE_ISSUE_LANE_OPS / 1e12, 3),
+            "frac_single_issue": round(achieved / SINGLE_ISSUE_LANE_OPS, 4),
+            "mix_ceiling": round(mix / 1e12, 3),
+            "mix_ceiling_waves_per_simd": waves_per_simd,
+            "frac_mix_ceiling": round(achieved / mix, 4),
+            "ops_per_launch": ops,
+        })
+    roofline.update({
+        "traffic": measured(counters, "hbm_bytes_per_launch"),
         "kernel": kname,
         "launches_per_batch": launches,
         "kernel_ms": round(per_launch * 1e3, 4),
         "blind_rotation_ms_per_batch": round(br_avg * 1e3, 3),
-        "ops_per_launch": ops,
         "hbm_algorithmic_bytes": hbm_alg,
         "hbm_frac": round(hbm_alg / per_launch / PEAK_HBM, 6),
         "kernel_source_sha256_16": source_hash(),
-    }
+    })
 
     legs = {"main_and_plain": round(time.perf_counter() - t_start, 1)}
     t_leg = time.perf_counter()
@@ -595,6 +626,7 @@ def margin_leg(args, binding, torch):
         row["blind_rotation_ms"] = round(float(np.mean(br_ms)), 3)
         row["keyswitch_ms"] = round(float(np.mean(ks_ms)), 3)
         ops = ops_per_bootstrap_wide(pw.n, pw.N, pw.l, r, pw.keys_per_coord) * Bm
+        # the butterfly method's operations per second, whichever kernels run
         row["blind_rotation_tops"] = round(ops / (row["blind_rotation_ms"] * 1e-3) / 1e12, 3)
         # the identity on Z_t: plaintext modulus 2t, two bootstraps
         ident = mctx.table_create_general(t, t, r, np.arange(t, dtype=np.uint32))

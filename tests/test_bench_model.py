@@ -33,3 +33,10 @@ def test_peaks():
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, "bench.py", "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode == 2 and "one GPU" in r.stdout
+
+
+def test_matrix_instructions():
+    # the counted figure of a batch of 4096 on k_mx_rotate<1,1> (SQ_INSTS_MFMA)
+    assert bench.matrix_insts_per_bootstrap(630, 4, 4) * 4096 == 2_312_110_080
+    assert bench.matrix_insts_per_bootstrap(1, 4, 1) == 224
+    assert round(bench.PEAK_MATRIX_INSTS * 65536 / 1e12) == 5033
