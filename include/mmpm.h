@@ -135,7 +135,9 @@ int mm_export_bsk(const mm_ctx *ctx, uint32_t *out, size_t words);
 int mm_export_ksk(const mm_ctx *ctx, uint32_t *out, size_t words);
 
 /* Select device `device`, convert the bootstrapping key to the NTT domain and
- * upload both keys.  Called implicitly by the first device call. */
+ * upload both keys, where the matrix-core kernels apply the bootstrapping key
+ * a second time in their order (where that copy does not fit the device, the other
+ * kernels run).  Called implicitly by the first device call. */
 int mm_device_init(mm_ctx *ctx, int device);
 
 /* Register a look-up table f: Z_t -> Z_t' held in r polynomials (Sec. 3,
@@ -270,9 +272,10 @@ int mm_last_timing(mm_ctx *ctx, float *blind_rotate_ms, float *keyswitch_ms);
  * shape, with its usual and with
  * twice the waves (N = 512, 1024), is a candidate for every batch the fused
  * kernel holds.  A batch on the global-accumulator path
- * (see mm_params; the wide modulus among others) has one or two blind-rotation
+ * (see mm_params; the wide modulus among others) has one to three blind-rotation
  * shapes (two primes: one workgroup per component, or per component and
- * prime; N = 16384: one workgroup per component, or the split ring): this call
+ * prime, of one or two digit groups; N = 1024: the matrix-core step or two digit
+ * groups; N = 16384: one workgroup per component, or the split ring): this call
  * times each shape once, then each key switch on the extracted samples. */
 int mm_autotune(mm_ctx *ctx, const int *table_ids, const uint32_t *ct_in, size_t count,
                 int *choice);
@@ -326,8 +329,8 @@ int mm_schedule_describe(mm_ctx *ctx, const int *table_ids, size_t count, int ch
  * every resident ciphertext of its partition by chunk_steps CMux steps (2/3 of
  * that for the wider ones when a partition holds both kinds), so a request
  * admitted while others run joins them at the next launch.  At N = 1024 a tick
- * whose partition holds at most two components per compute unit (four when it
- * holds r = 8 ciphertexts) runs the global-accumulator kernels instead, with the
+ * whose partition is light by the rule for untuned batches (see mm_autotune)
+ * runs the global-accumulator kernels instead, with the
  * four waves per component of the batched path's default, two digit groups of them
  * up to two components per compute unit (the accumulators then
  * live in two arenas, so the budget counts 2 x 2 x N words per component at

@@ -632,7 +632,9 @@ static uint32_t ks_lanes_splits(const mm_ctx &c, const Device &d, size_t count)
 // Key-switch schedule for `count` samples: one ciphertext per lane wherever a coordinate's
 // rows fit its LDS tile (n = 630, N = 1024, us, against the kernel that was best before: 1
 // sample 78 against 84, 33 82 against 654, 100 106 against 1433, 255 182 against 2456, 512 262
-// against 502 with at most 8 splits, 1000 484 against 644), else the i-split kernel.
+// against 502 with at most 8 splits, 1000 484 against 644; also at N = 4096 1 sample 236 against 432 and
+// 255 508 against 10264, at n = 64, N = 256 24 against 36 and 48 against 122, in base 2 at n = 200, N = 512
+// 51 against 106 and 120 against 1273), else the i-split kernel.
 KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 {
     KsSched k;
@@ -650,7 +652,8 @@ KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 // which reads only the rows their digits name.  The lane kernel reads the whole key, and the
 // next call's steps, each a launch that starts on the bootstrapping key in memory, run longer
 // for it (call of 1 ciphertext of r = 4 6.37 ms against 6.60, 16 of r = 8 6.65 against 6.80, 24
-// 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).
+// 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).  A
+// count, whatever the device: the rows that so many samples name are still a part of the key.
 KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count)
 {
     return count <= 16 ? KsSched{0, ks_splits(c, d, count)} : ks_default(c, d, count);
@@ -890,8 +893,10 @@ static Sched schedule_for(const mm_ctx &c, const Device &d, const int *ids, size
     if (comps <= 4 * cu && two_wave) return Sched{8, ks_default(c, d, count), 2};
     // rings of several waves per component: groups of four waves (two workgroups per compute
     // unit, each its own barriers) where the last round of eight-wave groups would be at most
-    // half full -- N = 4096, r = 1, ms: 2 ciphertexts 23.4 against 34.2, 256 28.9 against 39.5, 700
-    // 46.7 against 66.9; 512 34.6 either way, 1000 67.7 against 67.3
+    // half full -- N = 4096, r = 1, 630 steps, ms: 2 ciphertexts 23.4 against 34.2, 256 28.9 against 39.5, 700
+    // 46.7 against 66.9; 512 34.6 either way, 1000 67.7 against 67.3; N = 2048, 100 steps, 1 to 512
+    // components of r = 1, 2 or both 3.2 to 3.3 against 4.8 to 5.0 (ternary 6.0 to 6.2 against 9.0 to 9.2), 1100 to
+    // 1536 6.8 against 10.2 (12.8 against 18.9), 600 5.0 against 5.2
     const uint64_t wpp = (uint64_t)dev::waves_per_poly(c.p.N), round = 8 / std::min<uint64_t>(wpp, 8) * cu;
     const uint64_t rest = comps % round;
     if (wpp > 1 && max_r(c, ids, count) * wpp <= 4 && rest > 0 && 2 * rest <= round)

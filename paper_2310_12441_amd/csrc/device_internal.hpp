@@ -45,7 +45,7 @@ struct Device {
     uint32_t *bsk = nullptr, *bsk_corr = nullptr, *ksk = nullptr, *twf = nullptr, *twi = nullptr, *tv = nullptr;
     uint32_t *twf2 = nullptr, *twi2 = nullptr, qn2 = 0;  // second prime of a wide ring modulus
     uint32_t *twf_sub = nullptr, *twi_sub = nullptr;     // split rings: per-sub-ring twiddles
-    uint32_t *mx_cst = nullptr, *mx_bsk = nullptr;       // the matrix-core step: constants, key in its order
+    uint32_t *mx_cst = nullptr, *mx_bsk = nullptr;       // the matrix-core kernels: constants, key in their order (null: do not apply, or no room)
     size_t tv_words = 0, tables_uploaded = 0;
     DevBuf ws[WS_COUNT];
     PinBuf pin[2];

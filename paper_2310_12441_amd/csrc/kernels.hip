@@ -344,7 +344,8 @@ __global__ void __launch_bounds__(256) k_keyswitch(KsArgs A)
     }
 }
 
-// Key switch for large batches.  A workgroup (4 waves) owns 64 columns of the
+// Key switch with columns in lanes, a candidate of the autotuner (one ciphertext per lane has been
+// faster wherever measured: 4096 samples 1.7 ms against 6.8 to 44).  A workgroup (4 waves) owns 64 columns of the
 // output and 4 CPW ciphertexts; for each input coordinate i it stages the
 // l_ks x B_ks candidate rows KSK[i][*][*][cols] in LDS (double-buffered through
 // registers) and every wave adds, for each of its CPW ciphertexts, the l_ks rows
@@ -442,7 +443,7 @@ __global__ void __launch_bounds__(256) k_keyswitch_tiled(KsArgs A)
     }
 }
 
-// Key switch for large batches with one ciphertext per lane.  A workgroup
+// Key switch with one ciphertext per lane, the default.  A workgroup
 // (4 waves) owns 256 ciphertexts and 64 output columns; for each input
 // coordinate i it stages the l_ks x B_ks candidate rows KSK[i][*][*][cols] in
 // LDS (double-buffered through registers, rows padded to 66 words), and every

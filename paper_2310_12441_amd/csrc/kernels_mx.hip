@@ -402,7 +402,7 @@ __device__ __forceinline__ uint32_t mx_field(uint32_t src, uint32_t own, uint32_
 // two workgroup barriers per step (every rotation has read; every component is written).
 //
 // Bound by vector issue: a component's step is 3,440 vector and 224 matrix instructions
-// (71 % of the four-clock issue slots; the matrix unit is busy 34 % of the time and each of
+// (69 % of the four-clock issue slots; the matrix unit is busy 34 % of the time and each of
 // its instructions holds vector issue for about 12 clocks), at the 2.0 GHz the device runs
 // under this load.  Two waves per SIMD: 256 registers hold the 64-bit sums (64), two
 // polynomials' values and the key words in flight; LDS holds the constants (29 KB), the
@@ -546,10 +546,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // waves per pair as in k_mx_rotate, four pairs per workgroup, the key words shared by all.
 //
 // Bound by the chain of one wave (as a step of k_mx_rotate) up to one workgroup per compute
-// unit, by vector issue beyond.  Measured against k_external_product<1024>: 1 pair 10.2 us
-// against 24.9, 1000 15.5 against 31.3 (1.05 TB/s of pairs read and written), 4096 51.8 against
-// 92.3, 20,000 238 against 389.  With one wave per pair two workgroups share a compute unit
-// and one's loads run under the other's arithmetic (workgroups of eight pairs: 4096 in 56.3 us).
+// unit, by vector issue beyond.  Measured against k_external_product<1024>, us per call in a row,
+// pairs in the last-level cache / streamed through 1.2 GB: 1 pair 11.7 / 11.5 against 24.1, 1000 13.1 /
+// 15.8 (1.25 / 1.04 TB/s of pairs read and written) against 28.2 / 29.8, 4096 46.0 / 48.4 against 83.4 /
+// 84.5, 20,000 225 against 387.  With one wave per pair two workgroups share a compute unit and
+// one's loads run under the other's arithmetic (workgroups of eight pairs: 9 % longer at 4096).
 template <int W>
 __global__ __launch_bounds__(256 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mx_product(
     MxArgs X, const uint32_t *in, uint32_t *out, size_t count, uint32_t key, uint32_t Q, uint32_t qn, uint32_t log2B,
@@ -608,10 +609,12 @@ __global__ __launch_bounds__(256 * W) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // Bound by vector issue beside the matrix instructions (970 and 96 per product).  One workgroup
 // per compute unit of up to three waves per SIMD (165 registers); the constants (41 KB) are read
 // once, a wave takes further products in turn and requests the next one's operands before the
-// inverse.  Measured against k_negacyclic_mul<1024>: 3000 products 15.2 us (2.4 TB/s) against
-// 18.9; calls in a row 2048 12.5 against 14.8, 4096 21.5 against 26.9, 20,000 82.0 against
-// 106.8; up to 1024 equal (11.5 us, the host's part).  Workgroups of four waves, three per
-// compute unit, each with its own copy of the constants and no early requests: 20.0 us.
+// inverse.  Measured against k_negacyclic_mul<1024>, us per call in a row, operands in the last-level
+// cache (3000 products are 37 MB) / streamed through 1.2 GB: 3000 14.1 / 18.7 (2.6 / 2.0 TB/s) against
+// 17.9 / 20.5, 4096 19.8 / 21.6 against 23.4 / 25.9, 20,000 78.7 / 84.8 against 92.9 / 97.7; up to 2048
+// the host's part of a call, 13.4 either way.  Streamed operands gain less: nothing overlaps the
+// first round's loads.  Workgroups of four waves, three per compute unit, each with its own copy
+// of the constants and no early requests: 3000 in 20.0 us where this took 15.2.
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_mx_ring(
     MxArgs X, const uint32_t *a, const uint32_t *b, uint32_t *out, size_t count, uint32_t Q, uint32_t qn)
 {
@@ -1330,7 +1333,7 @@ void launch_mx_product(const MxArgs &X, const uint32_t *in, uint32_t *out, size_
                        uint32_t qn, uint32_t log2B, uint32_t l, uint32_t sg, hipStream_t st)
 {
     // two waves per pair while one round of workgroups (one per compute unit) takes them all: 1024
-    // pairs 15.6 us; the next pair would cost a second round, 1025 pairs take 23.6 us with one
+    // pairs 13.4 us; the next pair would cost a second round, 1025 pairs take 20.5 us with one
     const bool two = count <= 4 * X.num_cu;
     const dim3 grid((uint32_t)((count + 3) / 4));
     if (two) hipLaunchKernelGGL(k_mx_product<2>, grid, dim3(512), 0, st, X, in, out, count, key, Q, qn, log2B, l, sg);

@@ -25,9 +25,10 @@
 // split ring below), which the fused persistent kernel cannot hold, and, with
 // four waves per component at N = 1024, the faster shape for the lightest batches
 // (and, where the matrix-core kernels do not apply, the largest) the fused kernel
-// could hold.  Where the matrix-core kernels of kernels_mx.hip apply they take the
-// place of these steps (launch_wide_step).  Layouts are the wide ones with the
-// prime index dropped: a component is [part][N], key blocks [n][keys][2l][2][N].
+// could hold.  Where the matrix-core kernels of kernels_mx.hip apply, their step takes
+// the place of the usual number of waves here, and at N = 2048 their workgroups
+// per prime that of two digit groups (launch_wide_step).  Layouts are the wide ones with
+// the prime index dropped: a component is [part][N], key blocks [n][keys][2l][2][N].
 // Variants: two digit groups per workgroup (DG), one workgroup per prime (PS), and
 // an XCD-aware order of work items (xcd_item).
 #include <hip/hip_runtime.h>
