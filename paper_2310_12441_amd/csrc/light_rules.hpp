@@ -11,6 +11,7 @@ struct LightWork {
     uint32_t keys;   // RGSW keys per coordinate (2: ternary secret)
     uint64_t cu;     // compute units
     bool mx;         // the matrix-core kernels of one prime apply
+    bool beside = false;  // a fused kernel of other work runs at the same time (a server's other partition)
 };
 
 // The matrix-core kernel with two waves per component (630 steps, ms): up to four components
@@ -28,12 +29,14 @@ inline bool two_mx_waves(const LightWork &w)
 // One launch per step, four waves per component: beside the matrix-core kernels up to two
 // components per compute unit (r = 8, ms: 264 components 9.5 against 11.2 with one wave per
 // component, 512 9.9 against 11.2, 640 13.9 against 11.3; ternary 264 16.0 against 19.9, 512 16.4
-// against 20.0, 640 23.4 against 19.9); without them the batches that leave the device mostly idle:
+// against 20.0, 640 23.4 against 19.9), beside a fused kernel, whose workgroups hold their compute units for a
+// whole tick, up to one (16,000 requests/s of r = 1, 2, 4, 8, p50 of those of r = 8: 14.6 ms, 16.2 with up to
+// two; 10,000 11.3 and 10.8); without them the batches that leave the device mostly idle:
 // two components per compute unit, or four where the components cannot take two-wave slots (one
 // ciphertext 7.4 ms instead of 14.2 ms, or 25.9 ms at r = 8).
 inline bool steps_by_launch(const LightWork &w)
 {
-    if (w.mx) return !two_mx_waves(w) && w.comps <= 2 * w.cu;
+    if (w.mx) return !two_mx_waves(w) && w.comps <= (w.beside ? 1 : 2) * w.cu;
     return w.comps <= 2 * w.cu || (w.max_r > 4 && w.comps <= 4 * w.cu);
 }
 

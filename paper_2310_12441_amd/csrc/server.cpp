@@ -142,7 +142,7 @@ struct DevHost {
 struct Part {
     hipStream_t st = nullptr;
     hipEvent_t ev = nullptr;
-    bool busy = false;
+    bool busy = false, fused = false;  // a tick is in flight; the last one ran the fused kernel
     std::vector<Active> active, finishing;
     DevHost<dev::WaveTask> tasks;
     DevHost<int32_t> rows, stage_rows;
@@ -437,15 +437,19 @@ void Server::launch(Part &p)
     }
     bool glob = global;
     if (switchable) {
-        // the batched path's rule for light work
+        // the batched path's rule for light work, beside what the other partition has in flight
         uint64_t comps = 0;
         uint32_t max_r = 1;
         for (auto &a : p.active) {
             comps += c->tables[a.table].r;
             max_r = std::max(max_r, c->tables[a.table].r);
         }
-        glob = steps_by_launch(light_work(*c, d, comps, max_r));
+        LightWork work = light_work(*c, d, comps, max_r);
+        const Part &other = part[(&p - part) ^ 1];
+        work.beside = other.busy && other.fused;
+        glob = steps_by_launch(work);
     }
+    p.fused = !glob;
     if (glob) {
         launch_global(p, fresh);
         return;

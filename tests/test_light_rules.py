@@ -29,10 +29,14 @@ def test_matrix_cores(shape, keys):
     want = {(8, 8): STEPS, (264, 8): STEPS, (512, 8): STEPS, (513, 8): ONE, (4096, 8): ONE, (300, 5): STEPS,
             (4, 4): STEPS, (few, 4): STEPS, (few + 1, 4): TWO, (1024, 4): TWO, (1025, 4): ONE,
             (1, 1): TWO, (2, 2): TWO, (few + 1, 3): TWO, (1024, 2): TWO, (1026, 2): ONE}
-    assert shape([(c, r, keys, cu, 1) for c, r in want]) == list(want.values())
+    assert shape([(c, r, keys, cu, 1, 0) for c, r in want]) == list(want.values())
+    # a tick beside a fused one leaves its compute units to it: up to one component per compute unit
+    want.update({(264, 8): ONE, (512, 8): ONE, (300, 5): ONE, (256, 8): STEPS})
+    assert shape([(c, r, keys, cu, 1, 1) for c, r in want]) == list(want.values())
 
 
 def test_butterflies(shape):
     """Elsewhere: two components per compute unit, four where components cannot take two-wave slots."""
     want = {(4, 4): STEPS, (512, 4): STEPS, (513, 4): ONE, (513, 8): STEPS, (1024, 8): STEPS, (1025, 8): ONE}
-    assert shape([(c, r, 1, 256, 0) for c, r in want]) == list(want.values())
+    for beside in (0, 1):
+        assert shape([(c, r, 1, 256, 0, beside) for c, r in want]) == list(want.values())
