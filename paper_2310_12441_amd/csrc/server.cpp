@@ -603,7 +603,10 @@ void Server::launch_global(Part &p, const std::vector<Active> &fresh)
         }
         SRV_HIP(hipMemcpyAsync(p.woff.d, p.woff.h, F * 8, hipMemcpyHostToDevice, p.st));
         SRV_HIP(hipMemcpyAsync(p.qout.d, p.qout.h, F * 4, hipMemcpyHostToDevice, p.st));
-        const KsSched ks = ks_after_steps(*c, d, F);
+        // where nothing stays in the partition the next key switch is a whole blind rotation away, else one
+        // tick: there the lane kernel's shorter time counts for more than the steps it slows (5,000 and 10,000
+        // requests/s of r = 1, 2, 4, 8, p50 of those of r = 8: 9.3 and 11.3 ms, 10.0 and 13.2 by ks_after_steps)
+        const KsSched ks = p.active.empty() ? ks_after_steps(*c, d, F) : ks_default(*c, d, F);
         const size_t need = ks_part_words(*c, ks, F);
         if (p.part_cap < need || p.ext_cap < F) {
             SRV_HIP(hipStreamSynchronize(p.st));
