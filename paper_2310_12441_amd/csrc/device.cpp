@@ -654,9 +654,13 @@ KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 // for it (call of 1 ciphertext of r = 4 6.37 ms against 6.60, 16 of r = 8 6.65 against 6.80, 24
 // 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).  A
 // count, whatever the device: the rows that so many samples name are still a part of the key.
+// Only at one prime and N = 1024, whose bootstrapping key (41 MB at n = 630, 82 ternary) the 256 MB last-level
+// cache otherwise keeps: at the paper-margin parameters (268 MB) nothing is spared, and the lane kernel
+// is the faster one (calls of 1, 4, 16 of r = 1 9.0, 9.14, 9.18 ms against 9.0, 9.48, 9.58; one of r = 128 10.6, 10.7).
 KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count)
 {
-    return count <= 16 ? KsSched{0, ks_splits(c, d, count)} : ks_default(c, d, count);
+    if (count > 16 || c.wide || c.p.N != 1024) return ks_default(c, d, count);
+    return KsSched{0, ks_splits(c, d, count)};
 }
 
 size_t ks_part_words(const mm_ctx &c, const KsSched &k, size_t count) { return (size_t)k.P * count * (c.p.n + 1); }

@@ -26,7 +26,7 @@ inline bool two_mx_waves(const LightWork &w)
     return w.mx && w.max_r <= 4 && w.comps <= 4 * w.cu && (w.max_r <= 2 || w.comps > (w.keys == 2 ? 48u : 16u));
 }
 
-// One launch per step, four waves per component: beside the matrix-core kernels up to two
+// One launch per step, four waves per component: where the matrix-core kernels apply up to two
 // components per compute unit (r = 8, ms: 264 components 9.5 against 11.2 with one wave per
 // component, 512 9.9 against 11.2, 640 13.9 against 11.3; ternary 264 16.0 against 19.9, 512 16.4
 // against 20.0, 640 23.4 against 19.9), beside a fused kernel, whose workgroups hold their compute units for a

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from gpu_setup import Setup
-from synth import Params
+from synth import Params, Q2_DEFAULT
 
 pytestmark = pytest.mark.gpu
 
@@ -39,3 +39,15 @@ def test_per_step_schedules_at_1024(ternary):
             if count == 1:
                 np.testing.assert_array_equal(s.ctx.blind_rotate(ids, cts, s.p.n), acc)
     s.ctx.close()
+
+
+def test_key_switch_behind_steps():
+    """Up to 16 ciphertexts at one prime and N = 1024 the i-split key switch, which spares the cached
+    bootstrapping key; at two primes, whose key no cache keeps, the one by lanes."""
+    for p, few in ((Params(n=4, N=1024, log2_B=7, l=4), 0), (Params(n=4, N=2048, log2_B=15, l=4, Q2=Q2_DEFAULT), 2)):
+        s = Setup(p, 3150 + few)
+        for count, kernel in ((1, few), (16, few), (17, 2)):
+            ids, cts, want = s.batch([8] * count)
+            assert s.ctx.schedule_describe(ids)[4] == kernel, (p.N, count)
+            np.testing.assert_array_equal(s.ctx.bootstrap(ids, cts), want, err_msg=f"{p.N} {count}")
+        s.ctx.close()
