@@ -308,10 +308,10 @@ int mm_set_schedule(mm_ctx *ctx, const int *table_ids, size_t count, int choice)
  * that leave compute units idle (tables of r > 8 beside the matrix-core step: up to
  * 3/2 components per compute unit); 5, the global-accumulator path with two primes:
  * one workgroup per component and prime, the default up to 16 components per
- * compute unit; 6, those workgroups with two digit groups, N = 1024 and 2048,
+ * compute unit (beside the matrix-core kernels where those gain least, l < 4); 6, those workgroups with two digit groups, N = 1024 and 2048,
  * the default while all of them fit one per compute unit -- at N = 2048 with
- * log2_B <= 15 and l <= 4 the matrix-core kernel, up to 3/2 components per compute
- * unit, in place of 5).  Schedule 0 with workgroups of 8 waves and at most two waves
+ * log2_B <= 15 and l <= 4 the matrix-core kernel, with l = 4 or a ternary secret and
+ * l > 1 up to 3/2 components per compute unit in place of 5).  Schedule 0 with workgroups of 8 waves and at most two waves
  * per component (N = 1024), and on the global path with one wave per component (N = 1024)
  * or two primes (N = 2048), names the matrix-core kernels where they apply.  Any output
  * pointer may be NULL. */

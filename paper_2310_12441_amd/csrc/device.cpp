@@ -756,22 +756,23 @@ int light_global_wpp(const mm_ctx &c)
 // ternary, ms per bootstrap call, both shapes): one ciphertext 19.2 against 38.6,
 // 256 components 30.2 against 41.5, 1024 87.7 against 94.8, 4096 332.1 against
 // 335.3; 8192 669.2 against 663.2 (the shared digit fields computed twice).  Where the
-// matrix-core kernels apply (in place of the other shape and of two digit groups) up to 3/2:
-// 16 components 9.5 against 26.3, 256 18.5 against 26.8, 384 27.1 against 29.1, 512 36.0
-// against 32.1.
+// matrix-core kernels apply: two_prime_shape.
 bool prime_split(const mm_ctx &c, const Device &d, uint64_t comps)
 {
     const uint64_t cu = (uint64_t)d.num_cu;
-    return c.wide && dev::wide_supports_ps(c.p.N, 2) && (d.mx_cst ? 2 * comps <= 3 * cu : comps <= 16 * cu);
+    if (!c.wide || !dev::wide_supports_ps(c.p.N, 2)) return false;
+    return d.mx_cst ? two_prime_shape(comps, c.p.l, c.keys, cu) != 0 : comps <= 16 * cu;
 }
 
 // Digit groups of those workgroups: two (N = 1024, 2048) while both primes' workgroups
 // of every component fit one per compute unit (one ciphertext at N = 2048, t = 2^12:
-// 18.7 against 19.9 ms; 256 components 34.6 against 29.0 ms), else one.
+// 18.7 against 19.9 ms; 256 components 34.6 against 29.0 ms), else one.  On the matrix cores two name
+// their workgroups.
 int prime_split_dg(const mm_ctx &c, const Device &d, uint64_t comps)
 {
-    const bool fits = d.mx_cst || 2 * comps <= (uint64_t)d.num_cu;  // (matrix cores: 9.5 against 18.6 ms, any count)
-    return prime_split(c, d, comps) && dev::wide_supports_ps(c.p.N, 2, 2) && fits ? 2 : 1;
+    const uint64_t cu = (uint64_t)d.num_cu;
+    if (!prime_split(c, d, comps) || !dev::wide_supports_ps(c.p.N, 2, 2)) return 1;
+    return (d.mx_cst ? two_prime_shape(comps, c.p.l, c.keys, cu) == 6 : 2 * comps <= cu) ? 2 : 1;
 }
 
 // Digit groups per component of light global-path work: two (each group of
@@ -1180,8 +1181,8 @@ static void blind_rotate_wide(mm_ctx &c, Device &d, const int *ids, const uint32
     A.tasks = dt;
     A.ct_in = d_in;
     const uint32_t nt = (uint32_t)tasks.size();
-    // one prime: the schedule's shape; two: one workgroup per component whatever the count
-    A.acc_rd = enqueue_wide_rotation(c, A, acc0, acc1, nt, steps, st, S.ntt == 4 ? S.wpp : 0, S.ntt == 4 ? 2 : 1);
+    A.acc_rd = enqueue_wide_rotation(c, A, acc0, acc1, nt, steps, st, S.ntt == 3 ? 0 : S.wpp,
+                                     S.ntt == 4 || S.ntt == 6 ? 2 : 1, S.ntt == 5 || S.ntt == 6);
     if (c.wide) dev::launch_wide_export(c.p.N, A, nt, d_acc, st);
     else HIPC(hipMemcpyAsync(d_acc, A.acc_rd, words * 4, hipMemcpyDeviceToDevice, st));  // already [comp][part][N]
     HIPC(hipGetLastError());

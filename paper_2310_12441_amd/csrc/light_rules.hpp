@@ -1,4 +1,5 @@
-// Which shape takes light work at N = 1024: one rule for batches and for a server's ticks.
+// Which shape takes light work at N = 1024, and work of two primes at N = 2048: one rule for
+// batches and for a server's ticks.
 #pragma once
 
 #include <cstdint>
@@ -38,6 +39,30 @@ inline bool steps_by_launch(const LightWork &w)
 {
     if (w.mx) return !two_mx_waves(w) && w.comps <= (w.beside ? 1 : 2) * w.cu;
     return w.comps <= 2 * w.cu || (w.max_r > 4 && w.comps <= 4 * w.cu);
+}
+
+// Two primes at N = 2048 beside the matrix-core kernels: one matrix-core workgroup per component
+// and prime (6), the butterfly workgroup per component and prime (5), or the matrix-core step of two
+// components per workgroup (0).  5 and 6 take time by rounds of one component for every two
+// compute units, 0 by rounds of four times as many.  The matrix cores work on pairs of digits, an
+// odd length with a zero polynomial behind it, so they gain least at l = 1 and, with one key, at
+// l = 2 and 3.  100 steps, ms, one key unless said (components: 6 / 5 / 0):
+//   l = 1  128: 1.33 / 1.32 / 2.77, 384: 3.29 / 2.15 / 3.22, 1024: - / 4.86 / 5.71; two keys 384:
+//          4.02 / 3.10 / 4.03, 1024: - / 7.34 / 7.63
+//   l = 2  128: 1.35 / 1.61 / 2.75, 384: 3.29 / 2.77 / 3.18, 512: - / 3.55 / 3.39, 768: - / 4.97 / 5.59, 1024: -
+//          / 6.38 / 5.82; two keys 384: 4.12 / 4.39 / 4.06, 768: - / 8.08 / 7.74
+//   l = 3  128: 1.51 / 1.90 / 3.47, 384: 3.73 / 3.37 / 3.96, 512: - / 4.38 / 4.24, 768: - / 6.12 / 7.17, 1024: -
+//          / 7.89 / 7.41; two keys 384: 5.31 / 5.66 / 5.40
+//   l = 4  384: 3.77 / 4.00 / 3.91, 768: - / 7.29 / 7.28; two keys 384: 5.43 / 6.90 / 5.45, 768: - / 12.8 / 11.3
+inline int two_prime_shape(uint64_t comps, uint32_t l, uint32_t keys, uint64_t cu)
+{
+    const uint64_t rounds = (2 * comps + cu - 1) / cu;
+    if (rounds <= 1) return 6;
+    if (l == 1) return 5;
+    const bool lean = keys == 1 && l <= 3;
+    if (rounds <= 3) return lean ? 5 : 6;
+    const uint64_t last = (rounds - 1) % 4 + 1;  // of the step's last round, quarters
+    return lean && rounds <= 14 && last <= 2 ? 5 : 0;
 }
 
 }  // namespace mm

@@ -68,3 +68,21 @@ def test_two_primes_at_2048(l, log2_B, ternary):
     print("two primes l", l, "log2_B", log2_B, "ternary", ternary, flush=True)
     assert {k[2] for k in _each_shape(s, [1, 3, 1, 2])} == {0, 5, 6}
     s.ctx.close()
+
+
+@pytest.mark.parametrize("l,ternary,shapes", [(1, True, (6, 5, 5)), (2, False, (6, 5, 0)), (3, True, (6, 6, 0)), (4, False, (6, 6, 0))])
+def test_two_primes_at_2048_by_count(l, ternary, shapes):
+    """Up to one component for every two compute units, up to 3/2 per unit, and more: the untuned shape of
+    each, bootstraps against the oracle and blind rotations against the same ciphertexts in a small batch."""
+    s = Setup(Params(n=3, N=2048, log2_B=15, l=l, Q2=Q2_DEFAULT, ternary=ternary), 3700 + 10 * l + ternary)
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    few = s.ctx.blind_rotate(*s.batch([2] * 4)[:2], s.p.n).reshape(4, -1)
+    for count, shape in zip((cus // 4, cus // 4 + 1, cus * 3 // 4 + 1), shapes):
+        ids, cts, want = s.batch([2] * count)
+        print("two primes l", l, "ternary", ternary, "components", 2 * count, "shape", shape, flush=True)
+        assert s.default(ids)[2] == shape
+        np.testing.assert_array_equal(s.ctx.bootstrap(ids, cts), want)
+        acc = s.ctx.blind_rotate(ids, cts, s.p.n).reshape(count, -1)
+        np.testing.assert_array_equal(acc, few[np.arange(count) % 4])
+    s.ctx.close()

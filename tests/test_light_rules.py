@@ -17,9 +17,9 @@ def shape(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I" + os.path.join(ROOT, "paper_2310_12441_amd", "csrc"),
                     os.path.join(ROOT, "tests", "c", "light_rules.cpp"), "-o", exe], check=True)
 
-    def run(works):
+    def run(works, *args):
         text = "\n".join(" ".join(str(int(x)) for x in w) for w in works)
-        return subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split("\n")[:-1]
+        return subprocess.run([exe, *args], input=text, capture_output=True, text=True, check=True).stdout.split("\n")[:-1]
     return run
 
 
@@ -40,3 +40,19 @@ def test_butterflies(shape):
     want = {(4, 4): STEPS, (512, 4): STEPS, (513, 4): ONE, (513, 8): STEPS, (1024, 8): STEPS, (1025, 8): ONE}
     for beside in (0, 1):
         assert shape([(c, r, 1, 256, 0, beside) for c, r in want]) == list(want.values())
+
+
+def test_two_primes(shape):
+    """On the matrix cores (6, 0) except where the butterflies (5) measured faster: l = 1 above one component
+    for every two compute units, one key and l = 2 or 3 where the last round of 0 would be at most half full."""
+    want = {}
+    for l in (1, 2, 3, 4):
+        for keys in (1, 2):
+            lean = keys == 1 and l in (2, 3)
+            some = 5 if l == 1 or lean else 0
+            want.update({(1, l, keys): 6, (128, l, keys): 6, (129, l, keys): some or 6, (384, l, keys): some or 6,
+                         (385, l, keys): 5 if l == 1 else 0, (512, l, keys): 5 if l == 1 else 0, (513, l, keys): some,
+                         (768, l, keys): some, (769, l, keys): 5 if l == 1 else 0, (1792, l, keys): some,
+                         (2100, l, keys): 5 if l == 1 else 0, (8000, l, keys): 5 if l == 1 else 0})
+    got = shape([(c, l, k, 256) for c, l, k in want], "primes")
+    assert dict(zip(want, map(int, got))) == want
