@@ -264,6 +264,32 @@ static std::vector<uint32_t> mx_tables(const mm_ctx &c)
     return out;
 }
 
+// Arguments of the matrix-core kernels, once per key set.
+static dev::MxArgs mx_args(const mm_ctx &c, const Device &d)
+{
+    dev::MxArgs X{};
+    const mm_params &p = c.p;
+    uint32_t goff = 0;
+    for (uint32_t u = 0; u < p.l; u++) goff += (1u << (p.log2_B - 1)) << (u * p.log2_B);
+    X.cst = (const int32_t *)d.mx_cst;
+    X.bsk = (const int32_t *)d.mx_bsk;
+    X.bal64 = (int64_t)((uint64_t)0x80808080u << 32);
+    X.field = (goff << c.sg) - (p.Q - 1) / 2 + (c.sg ? 1u << (c.sg - 1) : 0u);
+    X.bias = (128u - (1u << (p.log2_B - 1))) * 0x01010101u;
+    X.bias16 = 128u - (1u << (p.log2_B - 1));
+    X.two16 = 65536;
+    auto shifts = [](uint32_t Q, int32_t &two32, int32_t &two48) {
+        two32 = centred(to_mont(1, Q), Q);
+        two48 = centred(mulmod(to_mont(1, Q), 65536 % Q, Q), Q);
+    };
+    shifts(p.Q, X.two32, X.two48);
+    if (c.wide) shifts(p.Q2, X.two32_1, X.two48_1);
+    X.ring = centred(to_mont(d.c_fix, p.Q), p.Q);
+    X.ring16 = centred(mulmod(to_mont(d.c_fix, p.Q), 65536 % p.Q, p.Q), p.Q);
+    X.num_cu = (uint32_t)d.num_cu;
+    return X;
+}
+
 void device_init(mm_ctx &c, int id)
 {
     if (c.dev && c.dev->id == id) return;
@@ -389,6 +415,7 @@ void device_init(mm_ctx &c, int id)
             }
             HIPC(hipGetLastError());
             HIPC(hipDeviceSynchronize());
+            d->mx = mx_args(c, *d);
         } else {
             d->mx_bsk = nullptr;
             if (block_cst) HIPC(hipFree(block_cst));
@@ -563,32 +590,6 @@ static dev::WaveTask *upload_tasks(Device &d, const std::vector<dev::WaveTask> &
     return dt;
 }
 
-dev::MxArgs mx_args(const mm_ctx &c, const Device &d)
-{
-    dev::MxArgs X{};
-    if (!d.mx_cst) return X;
-    const mm_params &p = c.p;
-    uint32_t goff = 0;
-    for (uint32_t u = 0; u < p.l; u++) goff += (1u << (p.log2_B - 1)) << (u * p.log2_B);
-    X.cst = (const int32_t *)d.mx_cst;
-    X.bsk = (const int32_t *)d.mx_bsk;
-    X.bal64 = (int64_t)((uint64_t)0x80808080u << 32);
-    X.field = (goff << c.sg) - (p.Q - 1) / 2 + (c.sg ? 1u << (c.sg - 1) : 0u);
-    X.bias = (128u - (1u << (p.log2_B - 1))) * 0x01010101u;
-    X.bias16 = 128u - (1u << (p.log2_B - 1));
-    X.two16 = 65536;
-    auto shifts = [](uint32_t Q, int32_t &two32, int32_t &two48) {
-        two32 = centred(to_mont(1, Q), Q);
-        two48 = centred(mulmod(to_mont(1, Q), 65536 % Q, Q), Q);
-    };
-    shifts(p.Q, X.two32, X.two48);
-    if (c.wide) shifts(p.Q2, X.two32_1, X.two48_1);
-    X.ring = centred(to_mont(d.c_fix, p.Q), p.Q);
-    X.ring16 = centred(mulmod(to_mont(d.c_fix, p.Q), 65536 % p.Q, p.Q), p.Q);
-    X.num_cu = (uint32_t)d.num_cu;
-    return X;
-}
-
 dev::BrArgs br_args(const mm_ctx &c, const Device &d)
 {
     dev::BrArgs A{};
@@ -607,7 +608,7 @@ dev::BrArgs br_args(const mm_ctx &c, const Device &d)
     A.twf = d.twf;
     A.twi = d.twi;
     A.tv = d.tv;
-    A.mx = mx_args(c, d);
+    A.mx = d.mx;
     return A;
 }
 
@@ -652,7 +653,8 @@ KsSched ks_default(const mm_ctx &c, const Device &d, size_t count)
 // which reads only the rows their digits name.  The lane kernel reads the whole key, and the
 // next call's steps, each a launch that starts on the bootstrapping key in memory, run longer
 // for it (call of 1 ciphertext of r = 4 6.37 ms against 6.60, 16 of r = 8 6.65 against 6.80, 24
-// 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels do not notice).  A
+// 7.10 against 6.86; ternary, 4 of r = 4, 10.8 against 11.3; the fused kernels of that ring do not notice, one
+// ciphertext at N = 8192 does at n = 100, 6.2 ms against 5.9, and not at n = 630, 38.5 against 39.2).  A
 // count, whatever the device: the rows that so many samples name are still a part of the key.
 // Only at one prime and N = 1024, whose bootstrapping key (41 MB at n = 630, 82 ternary) the 256 MB last-level
 // cache otherwise keeps: at the paper-margin parameters (268 MB) nothing is spared, and the lane kernel
@@ -1057,7 +1059,7 @@ dev::WideArgs wide_args(const mm_ctx &c, const Device &d)
     A.twf1 = d.twf2;
     A.twi1 = d.twi2;
     A.tv = d.tv;
-    A.mx = mx_args(c, d);
+    A.mx = d.mx;
     return A;
 }
 
@@ -1286,7 +1288,7 @@ void run_external_product(mm_ctx &c, uint32_t i, const uint32_t *in, size_t coun
     const uint32_t *din = stage_in(d, WS_IN, in, words, dptr, st);
     uint32_t *dout = stage_out(d, WS_OUT, out, words, dptr);
     if (d.mx_cst)
-        dev::launch_mx_product(mx_args(c, d), din, dout, count, i, c.p.Q, d.qn, c.p.log2_B, c.p.l, c.sg, st);
+        dev::launch_mx_product(d.mx, din, dout, count, i, c.p.Q, d.qn, c.p.log2_B, c.p.l, c.sg, st);
     else
         dev::launch_external_product(c.p.N, din, dout, count, d.bsk + (size_t)i * 4 * c.p.l * c.p.N, d.twf, d.twi,
                                      c.p.Q, d.qn, c.p.log2_B, c.p.l, c.sg, st);
@@ -1307,7 +1309,7 @@ void run_negacyclic_mul(mm_ctx &c, const uint32_t *a, const uint32_t *b, size_t 
     const uint32_t *db = stage_in(d, WS_IN2, b, words, dptr, st);
     uint32_t *dout = stage_out(d, WS_OUT, out, words, dptr);
     if (d.mx_cst && !c.wide)
-        dev::launch_mx_ring(mx_args(c, d), da, db, dout, count, c.p.Q, d.qn, st);
+        dev::launch_mx_ring(d.mx, da, db, dout, count, c.p.Q, d.qn, st);
     else
         dev::launch_negacyclic_mul(c.p.N, da, db, dout, count, d.twf, d.twi, c.p.Q, d.qn, d.c_fix, st);
     HIPC(hipGetLastError());

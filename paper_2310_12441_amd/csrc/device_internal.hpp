@@ -46,6 +46,7 @@ struct Device {
     uint32_t *twf2 = nullptr, *twi2 = nullptr, qn2 = 0;  // second prime of a wide ring modulus
     uint32_t *twf_sub = nullptr, *twi_sub = nullptr;     // split rings: per-sub-ring twiddles
     uint32_t *mx_cst = nullptr, *mx_bsk = nullptr;       // the matrix-core kernels: constants, key in their order (null: do not apply, or no room)
+    dev::MxArgs mx{};                                    // these kernels' arguments (cst null likewise)
     size_t tv_words = 0, tables_uploaded = 0;
     DevBuf ws[WS_COUNT];
     PinBuf pin[2];
@@ -111,7 +112,6 @@ struct Sched {
 
 std::vector<dev::WaveTask> pack_tasks(const std::vector<dev::WaveTask> &cts, uint32_t gw, uint32_t wpp,
                                       uint32_t cap = 0, uint64_t full = 0);
-dev::MxArgs mx_args(const mm_ctx &c, const Device &d);
 uint32_t spread_cap(const Device &d, uint64_t comps, uint32_t gw, uint32_t wpp);
 KsSched ks_default(const mm_ctx &c, const Device &d, size_t count);
 KsSched ks_after_steps(const mm_ctx &c, const Device &d, size_t count);  // behind one launch per step
